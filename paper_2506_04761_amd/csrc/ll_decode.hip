@@ -8,17 +8,30 @@
 // o_t = sum_l lambda_t^(l) S_t^(l) q_t (Eq. 3 read-out).
 //
 // Storage (one caller-owned buffer, carved by decode_layout):
-//   S      [B*H][L][d_v][d_k] fp32   levels 1 .. L-1 (slot 0 unused), each kept as c_l * S_stored
+//   S      [B*H][L][d_v][d_k] fp32   levels LOGW + 1 .. L-1, each kept as c_l * S_stored; the slots
+//                                    below them hold the head's window (DecodeWindow)
 //   scale  [2][B*H][L]        fp32   c_l, double-buffered by step parity (read t-1, write t)
-//   f0     [2][B*H][d_v + d_k] fp32  level 0 in factored form, v and k of the previous token
-// The decays are applied lazily through the per-level scales, so a step reads only the levels
-// that are not empty (scale != 0) and writes only the merged level p+1: O(popcount) level reads
-// and one level write per head instead of touching all L levels twice.
+//   f0     [2][B*H][d_v + d_k] fp32  unused (the buffer's size is part of the interface)
 //
-// Work split: grid (d_v / 16, B*H), 256 threads; thread (row r = tid / 16, part c = tid % 16)
-// owns d_v row 16 blockIdx.x + r and d_k entries [c d_k/16, (c+1) d_k/16) of every level; row
-// sums are reduced over the 16 lanes of the row.  Workgroups of one head share nothing but the
-// double-buffered scale and f0 arrays, written only by workgroup x = 0 into the other parity.
+// Window.  The tokens since the last multiple of W = 2^LOGW are kept as their rows of k and v, not
+// as matrices: within one aligned window no level above LOGW changes but for its decay, and the
+// levels 0 .. LOGW are sums over the window's own tokens,
+//     sum_{s in window, s <= t} lambda_t^(l(t,s)) (alpha_{s+1} .. alpha_t) (k_s . q_t) v_s.
+// The step that opens the next window (t % W == 0) merges the full window and the levels
+// LOGW + 1 .. p, p = lssb(t), into level p + 1.  So a step reads the nonempty levels above LOGW and
+// at most W rows, and writes a matrix once in W steps; kept as matrices, levels 1 .. LOGW cost half
+// of LOGW more level reads and one level write at every step.  The decays are applied lazily, through
+// one fp32 scale per level and one per window token (double-buffered by step parity like the scales).
+// W = 32 (8 for d = 16, where a row is not much smaller than a matrix).  Bound: reading the levels.  1024
+// heads, d = 128, bf16, positions 3000 .. 3031: 111 -> 64 us a step, 5 levels (335 MB) at 5.2 TB/s
+// against 8 read and one written.  W = 16, 32, 64 at positions 1984 .. 2111: 51.8, 50.0, 49.5 us
+// (1024 heads), 17.4, 18.5, 20.5 us (256 heads).
+//
+// Work split: grid (d_v / (16 RB), B*H), 256 threads; thread (row r = tid / 16, part c = tid % 16)
+// owns d_v rows 16 (RB blockIdx.x + i) + r, i < RB, and 16-byte pieces c, c + 16, .. of every d_k
+// row; row sums are reduced over the 16 lanes of the row.  Workgroups of one head share the window and
+// the scales, written only by workgroup x = 0: into slot t % W, which no other workgroup of the launch
+// reads, into the other parity, or into the other of the two window buffers.
 #include <type_traits>
 
 #include "../../include/libloglinear.h"
@@ -45,202 +58,561 @@ DecodeLayout decode_layout(int64_t B, int64_t H, int64_t dk, int64_t dv, int64_t
   return d;
 }
 
-template <typename T, int DK, int DV>
+// Sum over the 16 (8) lanes of a row, received by every lane (DPP; a row's lanes are active together).
+template <int CTRL>
+__device__ inline float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+__device__ inline float sum16(float x) {  // rotations by 8, 4, 2, 1
+  return dpp_add<0x121>(dpp_add<0x122>(dpp_add<0x124>(dpp_add<0x128>(x))));
+}
+__device__ inline float sum8(float x) {  // neighbours, pairs, then the mirrored half row
+  return dpp_add<0x141>(dpp_add<0x4e>(dpp_add<0xb1>(x)));
+}
+
+// A d_k row dealt to LANES lanes in pieces of VEC consecutive entries: lane c holds entries
+// LANES VEC j + VEC c .. + VEC - 1 of piece j, so that the lanes of a row read consecutive bytes.
+template <int DK, int LANES = 16>
+struct RowPart {
+  static constexpr int NPT = DK / LANES, VEC = NPT < 4 ? NPT : 4, PIECES = NPT / VEC;
+  static_assert(LANES * VEC * PIECES == DK, "whole pieces");
+  template <typename T>
+  __device__ static void load(const T* row, int c, float (&x)[NPT]) {
+    typedef T vec __attribute__((ext_vector_type(VEC)));
+#pragma unroll
+    for (int j = 0; j < PIECES; ++j) {
+      const vec y = *reinterpret_cast<const vec*>(row + LANES * VEC * j + VEC * c);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) x[VEC * j + e] = to_f32(y[e]);
+    }
+  }
+  template <typename T>
+  __device__ static void store(T* row, int c, const float (&x)[NPT]) {
+    typedef T vec __attribute__((ext_vector_type(VEC)));
+#pragma unroll
+    for (int j = 0; j < PIECES; ++j) {
+      vec y;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) y[e] = from_f32<T>(x[VEC * j + e]);
+      *reinterpret_cast<vec*>(row + LANES * VEC * j + VEC * c) = y;
+    }
+  }
+  __device__ static float dot(const float (&x)[NPT], const float (&y)[NPT]) {
+    float a = 0.f;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) a += x[i] * y[i];
+    return a;
+  }
+};
+
+template <int DK>
+constexpr int kLogWindow = DK == 16 ? 3 : 5;
+template <int DK>
+constexpr int kLogWindowGdn = DK == 16 ? 3 : 5;
+
+// One head's window, in its level slots 0 .. min(LOGW, L - 1) (levels 0 .. LOGW are never stored as
+// matrices).  Two buffers alternate by window, so that the step that opens a window can store its
+// token while other workgroups still read the full one.  With L - 1 < LOGW levels the state holds
+// fewer than W tokens and one buffer of 2^(L-1) slots is used.
+template <typename T, int DK, int DV, int LOG>
+struct DecodeWindow {
+  static constexpr int LOGW = LOG, W = 1 << LOG;
+  T *k, *v;              // [cap][d_k], [cap][d_v]
+  float *beta, *alpha;   // [cap] (Gated DeltaNet)
+  float* gram;           // [cap][cap] k_s . k_r for r < s (Gated DeltaNet)
+  static constexpr int buf_bytes(int cap) {
+    return (int)((cap * (DK + DV) * sizeof(T) + cap * 8 + cap * cap * 4 + 15) & ~size_t(15));
+  }
+  static constexpr int dec_bytes(int cap) { return (2 * (cap + 1) * 4 + 15) & ~15; }
+  static_assert(dec_bytes(W) + 2 * buf_bytes(W) <= (LOGW + 1) * DK * DV * 4, "the window fits in its levels' slots");
+  static_assert(dec_bytes(1) + buf_bytes(1) <= DK * DV * 4 && dec_bytes(2) + buf_bytes(2) <= 2 * DK * DV * 4 &&
+                    dec_bytes(W / 2) + buf_bytes(W / 2) <= LOGW * DK * DV * 4,
+                "so does a shorter one");
+  __device__ static int cap(int L) { return L - 1 >= LOGW ? W : 1 << (L - 1); }
+  // decays of the window's tokens up to the step of parity `par`, [cap]; then the whole window's
+  __device__ static float* dec(float* head, int L, int64_t par) { return head + (par & 1) * (cap(L) + 1); }
+  __device__ DecodeWindow(float* head, int L, int64_t window) {
+    const int n = cap(L);
+    char* p = reinterpret_cast<char*>(head) + dec_bytes(n) + (window & 1) * buf_bytes(n);
+    k = reinterpret_cast<T*>(p);
+    v = k + n * DK;
+    beta = reinterpret_cast<float*>(v + n * DV);
+    alpha = beta + n;
+    gram = alpha + n;
+  }
+};
+
+// The nonempty levels above `l0 - 1` (bit i of `rest`: level l0 + i), lowest first, KB at a time.
+template <int KB>
+struct LevelBatch {
+  int l[KB], n;
+  __device__ void next(int64_t& rest, int& l0) {
+    n = 0;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      l[b] = 0;
+      if (rest) {
+        const int sh = __builtin_ctzll((unsigned long long)rest);
+        l[b] = l0 + sh;
+        rest >>= sh + 1;
+        l0 += sh + 1;
+        n = b + 1;
+      }
+    }
+  }
+};
+
+template <typename T, int DK, int DV, int RB, bool MERGE>
 __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const float* __restrict__ log_alpha,
     const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, const float* __restrict__ scale_in,
-    float* __restrict__ scale_out, const float* __restrict__ f0_in, float* __restrict__ f0_out, int64_t t, int p,
-    int L) {
-  constexpr int NPT = DK / 16;  // d_k entries per thread
-  static_assert(DK % 16 == 0 && DV % 16 == 0, "whole 16-entry pieces");
+    float* __restrict__ scale_out, int64_t t, int L) {
+  typedef RowPart<DK> RP;
+  typedef DecodeWindow<T, DK, DV, kLogWindow<DK>> Win;
+  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW;
+  constexpr int KB = RB >= 4 ? 1 : 4;  // levels loaded together
+  __shared__ float p_s[W];
   const int64_t bh = blockIdx.y;
   const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
-  const int row = blockIdx.x * 16 + r;
-  const int n0 = c * NPT;
+  const int row0 = blockIdx.x * 16 * RB + r;  // rows row0 + 16 x
+  const int i = (int)(t & (W - 1));           // the token's slot; the window holds i tokens before it
+  float* Sh = S + bh * (int64_t)L * DV * DK;
+  const Win win(Sh, L, t >> LOGW);
+  const float* dec_in = Win::dec(Sh, L, t + 1);
+  float* dec_out = Win::dec(Sh, L, t);
+  const float* cin = scale_in + bh * L;
+  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
+  auto level_row = [&](int l, int x) { return Sh + ((int64_t)l * DV + row0 + 16 * x) * DK; };
 
   float qv[NPT], kv[NPT];
-#pragma unroll
-  for (int i = 0; i < NPT; ++i) {
-    qv[i] = to_f32(q[bh * DK + n0 + i]);
-    kv[i] = to_f32(k[bh * DK + n0 + i]);
-  }
-  const float vrow = to_f32(v[bh * DV + row]);
+  RP::load(q + bh * DK, c, qv);
+  RP::load(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]);
-  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
-  const float* cin = scale_in + bh * L;
-  float* Sh = S + bh * (int64_t)L * DV * DK;
-  auto level_row = [&](int l) { return Sh + ((int64_t)l * DV + row) * DK + n0; };
 
-  float acc = 0.f;  // this thread's part of sum_l lambda_l S^(l) q for its row
-  if (t > 0) {
-    // level p+1 <- levels 0..p (level 0 from the previous token's factors)
-    const float c0 = cin[0];
-    const float vold = f0_in[bh * (DV + DK) + row];
-    float m[NPT];
+  // levels that carry over, decayed by alpha_t; the first batch's rows are requested before the window
+  const int p = MERGE ? __builtin_ctzll((unsigned long long)t) : LOGW - 1;
+  int64_t rest = t >> (p + 1);
+  int l0 = p + 2;
+  LevelBatch<KB> lv;
+  float x[KB][RB][NPT];
+  auto load_levels = [&]() {
+    lv.next(rest, l0);
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) m[i] = c0 * vold * f0_in[bh * (DV + DK) + DV + n0 + i];
-    for (int l = 1; l <= p; ++l) {
+    for (int b = 0; b < KB; ++b)
+      if (b < lv.n)
+#pragma unroll
+        for (int y = 0; y < RB; ++y) RP::load(level_row(lv.l[b], y), c, x[b][y]);
+  };
+  load_levels();
+
+  // this lane's tokens c, c + 16, .. of the window: v at the rows, requested with the levels (clamped
+  // to slots of the buffer; those at or past i are not used)
+  constexpr int WV = (W + 15) / 16;
+  float vw[RB][WV];
+#pragma unroll
+  for (int y = 0; y < RB; ++y)
+#pragma unroll
+    for (int u = 0; u < WV; ++u) {
+      const int s = c + 16 * u < win.cap(L) ? c + 16 * u : win.cap(L) - 1;
+      vw[y][u] = to_f32(win.v[s * DV + row0 + 16 * y]);
+    }
+  float acc[RB];  // this thread's part of the rows' outputs
+#pragma unroll
+  for (int y = 0; y < RB; ++y) acc[y] = 0.f;
+  if constexpr (MERGE) {
+    // level p+1 <- levels LOGW+1 .. p and the full window
+    const Win full(Sh, L, (t >> LOGW) - 1);
+    float m[RB][NPT];
+#pragma unroll
+    for (int y = 0; y < RB; ++y)
+#pragma unroll
+      for (int e = 0; e < NPT; ++e) m[y][e] = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < W; ++s) {
+      const float d = dec_in[s];
+      float ks[NPT];
+      RP::load(full.k + s * DK, c, ks);
+#pragma unroll
+      for (int y = 0; y < RB; ++y) {
+        const float vs = d * to_f32(full.v[s * DV + row0 + 16 * y]);
+#pragma unroll
+        for (int e = 0; e < NPT; ++e) m[y][e] += vs * ks[e];
+      }
+    }
+    for (int l = LOGW + 1; l <= p; ++l) {
       const float cl = cin[l];
       if (cl == 0.f) continue;
-      const float* src = level_row(l);
 #pragma unroll
-      for (int i = 0; i < NPT; ++i) m[i] += cl * src[i];
-    }
-    float* dst = level_row(p + 1);
-    float d = 0.f;
+      for (int y = 0; y < RB; ++y) {
+        float z[NPT];
+        RP::load(level_row(l, y), c, z);
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) {
-      dst[i] = m[i];
-      d += m[i] * qv[i];
+        for (int e = 0; e < NPT; ++e) m[y][e] += cl * z[e];
+      }
     }
-    acc += lam_of(p + 1) * alpha * d;
-    // levels above p+1 carry over, decayed by alpha_t
-    for (int l = p + 2; l < L; ++l) {
-      const float cl = cin[l];
-      if (cl == 0.f) continue;
-      const float* src = level_row(l);
-      float e = 0.f;
+    const float w = lam_of(p + 1) * alpha;
 #pragma unroll
-      for (int i = 0; i < NPT; ++i) e += src[i] * qv[i];
-      acc += lam_of(l) * cl * alpha * e;
+    for (int y = 0; y < RB; ++y) {
+      RP::store(level_row(p + 1, y), c, m[y]);
+      acc[y] += w * RP::dot(m[y], qv);
     }
+  } else {
+    // the window's tokens: p_s = lambda^(l(t,s)) decay (k_s . q_t), 16 lanes per token
+    for (int s = r; s < i; s += 16) {
+      float ks[NPT];
+      RP::load(win.k + s * DK, c, ks);
+      const float a = sum16(RP::dot(ks, qv));
+      if (c == 0) {
+        const float d = dec_in[s] * alpha;
+        p_s[s] = lam_of(bitlen(uint32_t(i ^ s))) * d * a;
+        if (blockIdx.x == 0) dec_out[s] = d;
+      }
+    }
+    __syncthreads();
   }
-  // level 0 = v_t k_t^T: its contribution to the row is v_t[row] (k_t . q_t)
-  float kq = 0.f;
+  while (lv.n) {
 #pragma unroll
-  for (int i = 0; i < NPT; ++i) kq += kv[i] * qv[i];
+    for (int b = 0; b < KB; ++b)
+      if (b < lv.n) {
+        const float cl = cin[lv.l[b]];
+        if (cl == 0.f) continue;
+        const float w = lam_of(lv.l[b]) * cl * alpha;
 #pragma unroll
-  for (int off = 8; off > 0; off >>= 1) {
-    acc += __shfl_xor(acc, off, 64);
-    kq += __shfl_xor(kq, off, 64);
+        for (int y = 0; y < RB; ++y) acc[y] += w * RP::dot(x[b][y], qv);
+      }
+    load_levels();
   }
-  if (c == 0) o[bh * DV + row] = from_f32<T>(acc + lam_of(0) * vrow * kq);
+  // the token itself, level 0: v_t[row] (k_t . q_t)
+  const float kq = sum16(RP::dot(kv, qv));
+#pragma unroll
+  for (int y = 0; y < RB; ++y) {
+    const int row = row0 + 16 * y;
+    float a = acc[y];
+    if constexpr (!MERGE)
+#pragma unroll
+      for (int u = 0; u < WV; ++u)
+        if (c + 16 * u < i) a += p_s[c + 16 * u] * vw[y][u];
+    a = sum16(a);
+    if (c == 0) o[bh * DV + row] = from_f32<T>(a + lam_of(0) * to_f32(v[bh * DV + row]) * kq);
+  }
 
-  // next step's scales and level-0 factors (the other parity buffer)
+  // the next step's scales (the other parity buffer) and the token's window slot
   if (blockIdx.x == 0) {
     float* cout = scale_out + bh * L;
     for (int l = tid; l < L; l += kDecodeThreads) {
-      float x;
-      if (l == 0) x = 1.f;
-      else if (t == 0) x = 0.f;
-      else if (l <= p) x = 0.f;
-      else if (l == p + 1) x = alpha;
-      else x = cin[l] * alpha;
-      cout[l] = x;
+      // after token t level l >= 1 holds tokens iff bit l - 1 of t is set
+      const bool held = l > LOGW && ((t >> (l - 1)) & 1);
+      cout[l] = !held ? 0.f : (MERGE && l == p + 1) ? alpha : cin[l] * alpha;
     }
-    float* f = f0_out + bh * (DV + DK);
-    for (int i = tid; i < DV; i += kDecodeThreads) f[i] = to_f32(v[bh * DV + i]);
-    for (int i = tid; i < DK; i += kDecodeThreads) f[DV + i] = to_f32(k[bh * DK + i]);
+    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = k[bh * DK + e];
+    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = v[bh * DV + e];
+    if (tid == 0) dec_out[i] = 1.f;
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Log-linear Gated DeltaNet decoding.  The transition alpha_t (I - beta_t k_t k_t^T) is not a
-// scalar, so every nonempty level is rewritten each step; it acts on each d_v row of a level on
-// its own (row x -> alpha (x - beta (x . k) k)), which keeps the same row split as above.  After
-// token t the nonempty levels >= 1 are those l with bit l-1 of t set; for t >= 1 the lowest,
-// p + 1 (p = lssb(t)), is the sum of the previous step's levels 0 .. p.  The output reads every
-// level after its transition:
-//   o_t = lambda^(0) beta_t (k_t . q_t) v_t + sum_l lambda^(l) alpha_t (S^(l) q_t - beta_t (k_t . q_t) S^(l) k_t),
-// S^(l) being the level before the transition.  Storage as above; f0 holds beta v and k of the
-// previous token (level 0, factored); the scales are not used.
+// Log-linear Gated DeltaNet decoding.  The transition A_t = alpha_t (I - beta_t k_t k_t^T) acts on every
+// level; a token's part of the output is lambda_t^(l(t,s)) beta_s (k_s . A_{s+1} .. A_t q_t) v_s.  With
+// the window's tokens kept as rows (as above), the query is carried back through them instead of the
+// levels forward: with w_s = k_s . q^(s), q^(t) = q_t, q^(s-1) = q^(s) - beta_s w_s k_s (decays aside),
+//     w_s = k_s . q_t - sum_{r > s} beta_r w_r (k_r . k_s),
+// a triangular solve with the window's Gram matrix (one wave, one lane per token), and every level above
+// the window is read once with q~ = decay (q_t - sum_s beta_s w_s k_s), its matrix unchanged.  Applying
+// the transitions to every level at each token instead reads and writes all of them each step.  The
+// step that opens the next window (t % W == 0) applies the full window's W transitions to every level,
+// row by row in registers, adds the window's own tokens to the merged one and writes them all.
+// 1024 heads, d = 128, bf16, positions 3000 .. 3031: 208 -> 71 us a step on average, its merge about 290.
+// W = 16 against 32: 57.2 / 56.7 us (1024 heads, positions 1984 .. 2111), 20.8 / 23.5 (256 heads), 74.1 /
+// 70.5 (1024 heads, positions 3000 .. 3031).  Registers bound the waves in flight: the Gram rows in
+// registers instead of LDS, or spilling to 80 or 64 of them, cost 7 to 60 % of the step.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, int RB>
 __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const float* __restrict__ log_alpha,
-    const float* __restrict__ beta, const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S,
-    const float* __restrict__ f0_in, float* __restrict__ f0_out, int64_t t, int p, int L) {
-  constexpr int NPT = DK / 16;
-  static_assert(DK % 16 == 0 && DV % 16 == 0, "whole 16-entry pieces");
+    const float* __restrict__ beta, const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, int64_t t,
+    int L) {
+  typedef RowPart<DK> RP;
+  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
+  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW;
+  constexpr int KB = RB >= 4 ? 1 : 4;                 // levels loaded together
+  constexpr int QP = kDecodeThreads / DK < W ? kDecodeThreads / DK : W;  // partial sums of q~ per column
+  __shared__ __attribute__((aligned(16))) T k_s[W * DK];
+  __shared__ __attribute__((aligned(16))) float qp_s[QP * DK];
+  __shared__ float a_s[W], g_s[W], cf_s[W], p_s[W], gr_s[W * W + 64], db_s;  // gr_s: 64 lanes read a row
   const int64_t bh = blockIdx.y;
   const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
-  const int row = blockIdx.x * 16 + r;
-  const int n0 = c * NPT;
-  // sum over the 16 lanes of a row (every lane receives it)
-  auto row_sum = [](float x) {
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
-  };
+  const int row0 = blockIdx.x * 16 * RB + r;
+  const int i = (int)(t & (W - 1));
+  float* Sh = S + bh * (int64_t)L * DV * DK;
+  const Win win(Sh, L, t >> LOGW);
+  const int cap = Win::cap(L);
+  const float* dec_in = Win::dec(Sh, L, t + 1);
+  float* dec_out = Win::dec(Sh, L, t);
+  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
+  auto level_row = [&](int l, int x) { return Sh + ((int64_t)l * DV + row0 + 16 * x) * DK; };
 
   float qv[NPT], kv[NPT];
-#pragma unroll
-  for (int i = 0; i < NPT; ++i) {
-    qv[i] = to_f32(q[bh * DK + n0 + i]);
-    kv[i] = to_f32(k[bh * DK + n0 + i]);
-  }
-  const float vrow = to_f32(v[bh * DV + row]);
+  RP::load(q + bh * DK, c, qv);
+  RP::load(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]), bt = beta[bh];
-  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
-  float* Sh = S + bh * (int64_t)L * DV * DK;
-  auto level_row = [&](int l) { return Sh + ((int64_t)l * DV + row) * DK + n0; };
-  float kq = 0.f;
-#pragma unroll
-  for (int i = 0; i < NPT; ++i) kq += kv[i] * qv[i];
-  kq = row_sum(kq);
 
-  float acc = 0.f;  // the row's output (identical in the row's 16 lanes)
-  // transition of one level row x (this thread's part), written to dst, and its output term
-  auto step_level = [&](float (&x)[NPT], float* dst, int l) {
-    float a = 0.f, b = 0.f;
+  int64_t rest = t >> LOGW;
+  int l0 = LOGW + 1;
+  LevelBatch<KB> lv;
+  float x[KB][RB][NPT];
+  auto load_levels = [&]() {
+    lv.next(rest, l0);
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) {
-      a += x[i] * kv[i];
-      b += x[i] * qv[i];
-    }
-    a = row_sum(a);
-    b = row_sum(b);
+    for (int b = 0; b < KB; ++b)
+      if (b < lv.n)
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) dst[i] = alpha * (x[i] - bt * a * kv[i]);
-    acc += lam_of(l) * alpha * (b - bt * kq * a);
+        for (int y = 0; y < RB; ++y) RP::load(level_row(lv.l[b], y), c, x[b][y]);
   };
-  if (t > 0) {
-    // level p+1 <- previous levels 0 .. p (level 0 from the previous token's factors)
-    const float* f = f0_in + bh * (DV + DK);
-    const float bv = f[row];
+  load_levels();
+
+  // this lane's tokens c, c + 16, .. of the window: v at the rows, requested with the levels (clamped
+  // to slots of the buffer; those at or past i are not used)
+  constexpr int WV = (W + 15) / 16;
+  float vw[RB][WV];
+#pragma unroll
+  for (int y = 0; y < RB; ++y)
+#pragma unroll
+    for (int u = 0; u < WV; ++u) {
+      const int s = c + 16 * u < win.cap(L) ? c + 16 * u : win.cap(L) - 1;
+      vw[y][u] = to_f32(win.v[s * DV + row0 + 16 * y]);
+    }
+  for (int e = tid; e < i * cap; e += kDecodeThreads) gr_s[e] = win.gram[e];  // its first i rows
+  // wave 0: what the triangular solve needs besides, one token per lane
+  float bs = bt, dec = 1.f, lw = 0.f;
+  if (tid < i) {
+    bs = win.beta[tid];
+    dec = dec_in[tid] * alpha;
+  }
+  if (tid <= i) lw = lam_of(bitlen(uint32_t(i ^ tid)));
+
+  // ---- window: k_s . q_t and k_s . k_t for its tokens and the new one
+  for (int s = r; s <= i; s += 16) {
+    float ks[NPT];
+    if (s < i) RP::load(win.k + s * DK, c, ks);
+    else
+#pragma unroll
+      for (int e = 0; e < NPT; ++e) ks[e] = kv[e];
+    RP::store(k_s + s * DK, c, ks);
+    const float a = sum16(RP::dot(ks, qv)), g = sum16(RP::dot(ks, kv));
+    if (c == 0) {
+      a_s[s] = a;
+      g_s[s] = g;
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const float g = tid < i ? g_s[tid] : 0.f;
+    float w = tid <= i ? a_s[tid] : 0.f;
+    w -= bt * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), i)) * g;
+#pragma unroll
+    for (int s = W - 1; s >= 0; --s)
+      if (s < i)
+        w -= __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bs * w), s)) * (tid < s ? gr_s[s * cap + tid] : 0.f);
+    if (tid < W) {
+      cf_s[tid] = tid <= i ? bs * w : 0.f;
+      p_s[tid] = lw * dec * bs * w;
+    }
+    const float db = i ? dec_in[cap] * alpha : alpha;  // decay of the whole window
+    if (tid == 0) db_s = db;
+    if (blockIdx.x == 0 && tid <= i) {
+      dec_out[tid] = dec;
+      if (tid < i) win.gram[i * cap + tid] = g;
+      if (tid == i) {
+        win.beta[i] = bt;
+        win.alpha[i] = alpha;
+        dec_out[cap] = db;
+      }
+    }
+  }
+  __syncthreads();
+  if (QP * DK == kDecodeThreads || tid < QP * DK) {
+    const int n = tid % DK;
+    float a = 0.f;
+#pragma unroll
+    for (int u = 0; u < W / QP; ++u) {  // past token i: weight 0
+      const int s = tid / DK + QP * u;
+      a += cf_s[s] * to_f32(k_s[(s < i ? s : i) * DK + n]);
+    }
+    qp_s[tid] = a;
+  }
+  __syncthreads();
+  float qt[NPT];
+  {
+    const float db = db_s;
+#pragma unroll
+    for (int e = 0; e < NPT; ++e) qt[e] = qv[e];
+#pragma unroll
+    for (int y = 0; y < QP; ++y) {
+      float z[NPT];
+      RP::load(qp_s + y * DK, c, z);
+#pragma unroll
+      for (int e = 0; e < NPT; ++e) qt[e] -= z[e];
+    }
+#pragma unroll
+    for (int e = 0; e < NPT; ++e) qt[e] *= db;
+  }
+
+  // ---- levels above the window, read with q~
+  float acc[RB];
+#pragma unroll
+  for (int y = 0; y < RB; ++y) acc[y] = 0.f;
+  while (lv.n) {
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+      if (b < lv.n) {
+        const float w = lam_of(lv.l[b]);
+#pragma unroll
+        for (int y = 0; y < RB; ++y) acc[y] += w * RP::dot(x[b][y], qt);
+      }
+    load_levels();
+  }
+#pragma unroll
+  for (int y = 0; y < RB; ++y) {
+    const int row = row0 + 16 * y;
+    float a = acc[y];
+#pragma unroll
+    for (int u = 0; u < WV; ++u)
+      if (c + 16 * u < i) a += p_s[c + 16 * u] * vw[y][u];
+    a = sum16(a);
+    if (c == 0) o[bh * DV + row] = from_f32<T>(a + p_s[i] * to_f32(v[bh * DV + row]));
+  }
+  if (blockIdx.x == 0) {
+    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = k[bh * DK + e];
+    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = v[bh * DV + e];
+  }
+}
+
+// Token t with t % W == 0, t > 0: every level through the full window's transitions (row x of a level:
+// x <- x - beta_s (x . k_s) k_s for s in order, then the window's decay), then token t as the first of
+// its window.  The merged level p + 1 is the sum of levels LOGW + 1 .. p before them and of the window's
+// tokens, which enter in turn (x <- alpha_s (x - beta_s (x . k_s) k_s) + beta_s v_s[row] k_s).
+// 8 lanes per row: the 2 DK / 8 multiplications and additions of a transition outweigh the lanes' sum
+// (16 lanes: 414 us for 6 levels of 1024 heads, d = 128; 8: 290).
+constexpr int kMergeLanes = 8;
+
+template <typename T, int DK, int DV>
+__global__ __launch_bounds__(DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads) void
+k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                   const float* __restrict__ log_alpha, const float* __restrict__ beta, const float* __restrict__ lam,
+                   T* __restrict__ o, float* __restrict__ S, int64_t t, int L) {
+  typedef RowPart<DK, kMergeLanes> RP;
+  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
+  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW, NB = 4;
+  constexpr int NTH = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads, ROWS = NTH / kMergeLanes;
+  __shared__ __attribute__((aligned(16))) float k_s[W * DK];
+  __shared__ float bv_s[W * ROWS], b_s[W], al_s[W];
+  const int64_t bh = blockIdx.y;
+  const int tid = threadIdx.x, r = tid / kMergeLanes, c = tid % kMergeLanes;
+  const int row = blockIdx.x * ROWS + r;
+  float* Sh = S + bh * (int64_t)L * DV * DK;
+  const Win full(Sh, L, (t >> LOGW) - 1), win(Sh, L, t >> LOGW);
+  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
+  auto level_row = [&](int l) { return Sh + ((int64_t)l * DV + row) * DK; };
+  const int p = __builtin_ctzll((unsigned long long)t);
+
+  for (int s = r; s < W; s += ROWS) {
+    float ks[NPT];
+    RP::load(full.k + s * DK, c, ks);
+    RP::store(k_s + s * DK, c, ks);
+  }
+  for (int e = tid; e < W * ROWS; e += NTH)
+    bv_s[e] = full.beta[e / ROWS] * to_f32(full.v[e / ROWS * DV + blockIdx.x * ROWS + e % ROWS]);
+  for (int s = tid; s < W; s += NTH) {
+    b_s[s] = full.beta[s];
+    al_s[s] = full.alpha[s];
+  }
+  float qt[NPT], kv[NPT];  // q~ = alpha_t (q - beta_t (k . q) k)
+  RP::load(q + bh * DK, c, qt);
+  RP::load(k + bh * DK, c, kv);
+  const float alpha = expf(log_alpha[bh]), bt = beta[bh];
+  const float kq = sum8(RP::dot(kv, qt));
+#pragma unroll
+  for (int e = 0; e < NPT; ++e) qt[e] = alpha * (qt[e] - bt * kq * kv[e]);
+  const float dw = Win::dec(Sh, L, t + 1)[Win::cap(L)];  // decay of the full window
+
+  // levels lowest first: the merged one, then the carried ones, NB at a time
+  float acc = 0.f;
+  int64_t rest = t >> (p + 1);
+  int l0 = p + 2;
+  LevelBatch<NB> lv;
+  float x[NB][NPT];
+  auto load_levels = [&]() {
+    lv.next(rest, l0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < lv.n) RP::load(level_row(lv.l[b]), c, x[b]);
+  };
+  load_levels();
+  {
     float m[NPT];
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) m[i] = bv * f[DV + n0 + i];
-    for (int l = 1; l <= p; ++l) {
-      const float* src = level_row(l);
+    for (int e = 0; e < NPT; ++e) m[e] = 0.f;
+    for (int l = LOGW + 1; l <= p; ++l) {
+      float z[NPT];
+      RP::load(level_row(l), c, z);
 #pragma unroll
-      for (int i = 0; i < NPT; ++i) m[i] += src[i];
+      for (int e = 0; e < NPT; ++e) m[e] += z[e];
     }
-    step_level(m, level_row(p + 1), p + 1);
-    // the other nonempty levels (bits above p of t) carry over, transitioned in place; their
-    // rows are loaded kBatch levels at a time before any is processed (independent loads)
-    constexpr int kBatch = 4;
-    int64_t rest = t >> (p + 1);  // bit i: level p + 2 + i is nonempty
-    int l0 = p + 2;
-    while (rest) {
-      int lv[kBatch];
-      int n = 0;
-      while (rest && n < kBatch) {
-        const int sh = __builtin_ctzll((unsigned long long)rest);
-        lv[n++] = l0 + sh;
-        rest >>= sh + 1;
-        l0 += sh + 1;
-      }
-      float x[kBatch][NPT];
+    __syncthreads();
+#pragma unroll 2
+    for (int s = 0; s < W; ++s) {
+      float ks[NPT];
+      RP::load(k_s + s * DK, c, ks);
+      const float al = al_s[s];
+      const float y = bv_s[s * ROWS + r] - al * b_s[s] * sum8(RP::dot(m, ks));
 #pragma unroll
-      for (int b = 0; b < kBatch; ++b)
-        if (b < n) {
-          const float* src = level_row(lv[b]);
-#pragma unroll
-          for (int i = 0; i < NPT; ++i) x[b][i] = src[i];
-        }
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b)
-        if (b < n) step_level(x[b], level_row(lv[b]), lv[b]);
+      for (int e = 0; e < NPT; ++e) m[e] = al * m[e] + y * ks[e];
     }
+    RP::store(level_row(p + 1), c, m);
+    acc += lam_of(p + 1) * RP::dot(m, qt);
   }
-  // level 0 = beta_t v_t k_t^T: its term is beta_t v_t[row] (k_t . q_t)
-  if (c == 0) o[bh * DV + row] = from_f32<T>(acc + lam_of(0) * bt * vrow * kq);
+  while (lv.n) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)  // a short batch: the rows past it are not used
+      if (b >= lv.n)
+#pragma unroll
+        for (int e = 0; e < NPT; ++e) x[b][e] = 0.f;
+#pragma unroll 2
+    for (int s = 0; s < W; ++s) {
+      float ks[NPT];
+      RP::load(k_s + s * DK, c, ks);
+      const float bs = b_s[s];
+      float y[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) y[b] = -bs * sum8(RP::dot(x[b], ks));
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < NPT; ++e) x[b][e] += y[b] * ks[e];
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < lv.n) {
+#pragma unroll
+        for (int e = 0; e < NPT; ++e) x[b][e] *= dw;
+        RP::store(level_row(lv.l[b]), c, x[b]);
+        acc += lam_of(lv.l[b]) * RP::dot(x[b], qt);
+      }
+    load_levels();
+  }
+  acc = sum8(acc);
+  if (c == 0) o[bh * DV + row] = from_f32<T>(acc + lam_of(0) * bt * to_f32(v[bh * DV + row]) * kq);
 
   if (blockIdx.x == 0) {
-    float* f = f0_out + bh * (DV + DK);
-    for (int i = tid; i < DV; i += kDecodeThreads) f[i] = bt * to_f32(v[bh * DV + i]);
-    for (int i = tid; i < DK; i += kDecodeThreads) f[DV + i] = to_f32(k[bh * DK + i]);
+    for (int e = tid; e < DK; e += NTH) win.k[e] = k[bh * DK + e];
+    for (int e = tid; e < DV; e += NTH) win.v[e] = v[bh * DV + e];
+    if (tid == 0) {
+      win.beta[0] = bt;
+      win.alpha[0] = alpha;
+      float* dec_out = Win::dec(Sh, L, t);
+      dec_out[0] = 1.f;
+      dec_out[Win::cap(L)] = alpha;
+    }
   }
 }
 
@@ -250,21 +622,35 @@ __global__ void k_zero_f32(float* __restrict__ p, int64_t n) {
   if (i < n) p[i] = 0.f;
 }
 
+// Rows of d_v per workgroup, in 16s: 4 once that still gives every CU several workgroups (a window's
+// scores are formed once per workgroup), else 1, so that a small batch spreads over the chip.
+// d = 128, 16 against 64 rows: 53.7 / 50.0 us and 29.1 / 25.9 us (Mamba-2, 1024 and 512 heads), 80.3 / 61.6
+// and 44.0 / 31.7 us (Gated DeltaNet); 256 heads or fewer keep 16.
+template <int DV>
+bool decode_wide(int64_t BH) {
+  return DV % 64 == 0 && BH * (DV / 64) >= 1024;
+}
+
 template <typename T, int DK, int DV>
 hipError_t launch_decode(const void* q, const void* k, const void* v, const float* log_alpha, const float* lambda,
                          void* o, void* state, int64_t t, int64_t B, int64_t H, int L, hipStream_t st) {
+  typedef DecodeWindow<T, DK, DV, kLogWindow<DK>> Win;
   const DecodeLayout d = decode_layout(B, H, DK, DV, L);
   char* base = static_cast<char*>(state);
   const int64_t BH = B * H;
   float* S = reinterpret_cast<float*>(base + d.S);
   float* scale = reinterpret_cast<float*>(base + d.scale);
-  float* f0 = reinterpret_cast<float*>(base + d.f0);
   const int par = (int)(t & 1);
-  const int p = t > 0 ? __builtin_ctzll((unsigned long long)t) : 0;
-  hipLaunchKernelGGL((k_decode_step<T, DK, DV>), dim3(DV / 16, (unsigned)BH), dim3(kDecodeThreads), 0, st,
-                     (const T*)q, (const T*)k, (const T*)v, log_alpha, lambda, (T*)o, S,
-                     scale + (1 - par) * BH * L, scale + par * BH * L, f0 + (1 - par) * BH * (DV + DK),
-                     f0 + par * BH * (DV + DK), t, p, L);
+  const bool merge = t > 0 && t % Win::W == 0;
+  constexpr int RW = DV % 64 == 0 ? 4 : 1;
+  auto launch = [&](auto kernel, int rb) {
+    hipLaunchKernelGGL(kernel, dim3(DV / (16 * rb), (unsigned)BH), dim3(kDecodeThreads), 0, st, (const T*)q,
+                       (const T*)k, (const T*)v, log_alpha, lambda, (T*)o, S, scale + (1 - par) * BH * L,
+                       scale + par * BH * L, t, L);
+  };
+  if (merge) launch(k_decode_step<T, DK, DV, 1, true>, 1);
+  else if (decode_wide<DV>(BH)) launch(k_decode_step<T, DK, DV, RW, false>, RW);
+  else launch(k_decode_step<T, DK, DV, 1, false>, 1);
   return hipGetLastError();
 }
 
@@ -272,16 +658,20 @@ template <typename T, int DK, int DV>
 hipError_t launch_gdn_decode(const void* q, const void* k, const void* v, const float* log_alpha, const float* beta,
                              const float* lambda, void* o, void* state, int64_t t, int64_t B, int64_t H, int L,
                              hipStream_t st) {
+  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
   const DecodeLayout d = decode_layout(B, H, DK, DV, L);
-  char* base = static_cast<char*>(state);
   const int64_t BH = B * H;
-  float* S = reinterpret_cast<float*>(base + d.S);
-  float* f0 = reinterpret_cast<float*>(base + d.f0);
-  const int par = (int)(t & 1);
-  const int p = t > 0 ? __builtin_ctzll((unsigned long long)t) : 0;
-  hipLaunchKernelGGL((k_gdn_decode_step<T, DK, DV>), dim3(DV / 16, (unsigned)BH), dim3(kDecodeThreads), 0, st,
-                     (const T*)q, (const T*)k, (const T*)v, log_alpha, beta, lambda, (T*)o, S,
-                     f0 + (1 - par) * BH * (DV + DK), f0 + par * BH * (DV + DK), t, p, L);
+  float* S = reinterpret_cast<float*>(static_cast<char*>(state) + d.S);
+  const bool merge = t > 0 && t % Win::W == 0;
+  constexpr int RW = DV % 64 == 0 ? 4 : 1;
+  auto launch = [&](auto kernel, int threads, int rows) {  // rows of d_v per workgroup
+    hipLaunchKernelGGL(kernel, dim3(DV / rows, (unsigned)BH), dim3(threads), 0, st, (const T*)q, (const T*)k,
+                       (const T*)v, log_alpha, beta, lambda, (T*)o, S, t, L);
+  };
+  constexpr int MT = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads;
+  if (merge) launch(k_gdn_decode_merge<T, DK, DV>, MT, MT / kMergeLanes);
+  else if (decode_wide<DV>(BH)) launch(k_gdn_decode_step<T, DK, DV, RW>, kDecodeThreads, 16 * RW);
+  else launch(k_gdn_decode_step<T, DK, DV, 1>, kDecodeThreads, 16);
   return hipGetLastError();
 }
 

@@ -1,0 +1,120 @@
+"""Decoding at the edges of the token window (the tokens since the last multiple of W = 32, or 8 for
+d = 16, are kept as rows; the step that opens a window merges the last one): states of few levels,
+whose window is shorter than W, sequences around one and several merges, a gate that resets the
+state, the kernels with 64 rows of d_v per workgroup (large batches) and a state copied in the
+middle of a window.  References and bars are those of test_gpu_decode.py and test_gpu_gdn_decode.py:
+the float64 oracle, normalised max error 1e-4 (fp32) and 2e-2 (bf16)."""
+
+import numpy as np
+import pytest
+
+from oracle import fenwick, gdn, mamba2
+from synthetic import WORKLOADS, generate
+from tests.gpu_util import rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+DIST = {"mamba2": "slow", "gdn": "gdn_slow"}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2506_04761_amd  # noqa: F401
+
+
+def inputs(variant, dtype, d, T, H=3, seed=0):
+    w = WORKLOADS["ll_gdn_bf16_T8192" if variant == "gdn" else "ll_mamba2_bf16_T65536"]
+    return generate(w.with_(dtype=dtype, B=1, H=H, T=T, dk=d[0], dv=d[1], C=16, dist=DIST[variant], seed=seed + T))
+
+
+class Decoder:
+    """One state fed token by token with the rows of x."""
+
+    def __init__(self, variant, x, dtype, L, rep=1):
+        import torch
+        import paper_2506_04761_amd as ll
+        self.ll, self.torch, self.variant, self.L = ll, torch, variant, L
+        rows = lambda n, dt: to_dev(np.repeat(x[n][0], rep, axis=1), dt).unsqueeze(1)  # [T, 1, H rep, ...]
+        self.a = {n: rows(n, dtype) for n in ("q", "k", "v")}
+        self.a.update({n: rows(n, "f32") for n in ("log_alpha", "lam", "beta") if n in x})
+        T, B, H, dk = self.a["q"].shape
+        dv = self.a["v"].shape[-1]
+        self.state = torch.full((ll.ll_decode_state_bytes(B, H, dk, dv, L),), 0xFF, dtype=torch.uint8, device="cuda")
+        init = ll.ll_gdn_decode_init if variant == "gdn" else ll.ll_mamba2_decode_init
+        init(self.state, B, H, dk, dv, L, self.a["q"].dtype)
+
+    def feed(self, t0, t1, state=None):
+        state = self.state if state is None else state
+        outs = []
+        for t in range(t0, t1):
+            y = {n: z[t] for n, z in self.a.items()}
+            if self.variant == "gdn":
+                o = self.ll.ll_gdn_decode_step(y["q"], y["k"], y["v"], y["log_alpha"], y["beta"], y["lam"], state, t, self.L)
+            else:
+                o = self.ll.ll_mamba2_decode_step(y["q"], y["k"], y["v"], y["log_alpha"], y["lam"], state, t, self.L)
+            outs.append(o[0].float())
+        self.torch.cuda.synchronize()
+        return self.torch.stack(outs).cpu().numpy().astype(np.float64)  # [T, H, d_v]
+
+
+def reference(variant, x):
+    if variant == "gdn":
+        return gdn.recurrent(x["q"], x["k"], x["v"], x["log_alpha"], x["beta"], x["lam"])[0]
+    return mamba2.recurrent(x["q"], x["k"], x["v"], x["log_alpha"], x["lam"])[0]
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+@pytest.mark.parametrize("dtype,d,Ts", [
+    ("f32", (16, 16), (1, 2, 4, 8, 9, 16, 17, 64, 65)),
+    ("f32", (64, 64), (1, 2, 16, 32, 33, 130)),
+    ("bf16", (64, 64), (4, 32, 65)),
+    ("bf16", (128, 64), (1, 8, 33, 97)),
+    ("bf16", (128, 128), (2, 31, 32, 64, 161)),
+])
+def test_window_edges(variant, dtype, d, Ts):
+    for T in Ts:
+        x = inputs(variant, dtype, d, T)
+        err = rel_err(Decoder(variant, x, dtype, fenwick.num_levels(T)).feed(0, T), reference(variant, x))
+        print(f"{variant} {dtype} {d} T={T}: {err:.2e}", flush=True)
+        assert err <= TOL[dtype], (T, err)
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+def test_reset_gate(variant):
+    """log_alpha = -inf (alpha = 0) forgets everything before its token: inside a window, at the merge
+    and after it."""
+    x = inputs(variant, "f32", (64, 64), 100)
+    for t in (20, 63, 64, 70):
+        x["log_alpha"][:, t] = -np.inf
+    ref = reference(variant, x)
+    got = Decoder(variant, x, "f32", fenwick.num_levels(100)).feed(0, 100)
+    assert np.isfinite(got).all() and rel_err(got, ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+@pytest.mark.parametrize("d", [(64, 64), (128, 64), (128, 128)])
+def test_large_batch(variant, d):
+    """1026 heads take the 64-row workgroups, 3 the 16-row ones: each of the 342 copies of a head
+    gives the same row bit for bit, within the bar of the oracle."""
+    T = 70
+    x = inputs(variant, "bf16", d, T)
+    x = dict(x, lam=np.concatenate([x["lam"], np.ones(x["lam"].shape[:-1] + (1,), np.float32)], axis=-1))
+    got = Decoder(variant, x, "bf16", x["lam"].shape[-1], rep=342).feed(0, T).reshape(T, 3, 342, d[1])
+    assert (got == got[:, :, :1]).all()
+    assert rel_err(got[:, :, 0], reference(variant, x)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+def test_copied_state(variant):
+    """A state copied in the middle of a window continues like the original, and the original is not
+    touched by the copy's steps."""
+    x = inputs(variant, "bf16", (128, 128), 110)
+    dec = Decoder(variant, x, "bf16", fenwick.num_levels(110))
+    dec.feed(0, 77)
+    fork = dec.state.clone()
+    a, b = dec.feed(77, 110, fork), dec.feed(77, 110)
+    assert (a == b).all() and rel_err(b, reference(variant, x)[77:]) <= TOL["bf16"]
