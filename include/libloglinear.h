@@ -126,7 +126,8 @@ ll_status ll_mamba2_fwd_grouped(const void* q, const void* k, const void* v, con
  * (hipEvent_t handles passed as void*) on `stream`, events[i] right before kernel stage i and
  * events[3] after the last stage, so that the caller can read each stage's duration with
  * hipEventElapsedTime once the stream has passed them.  Stages of the single-pass path (bf16,
- * C = 64): 0 tile totals of the log-gates, 1 aligned block sums of those totals, 2 the tile
+ * C = 64): 0 tile totals of the log-gates, 1 aligned block sums of those totals (nothing up to
+ * T = 8192), 2 the tile
  * kernel (states, Fenwick nodes, intra-tile and inter-tile terms).  Stages of the three-kernel
  * path: 0 tile states and the summaries of the lowest three tile levels, 1 scan (the block tree
  * of summaries above them; with lambda == NULL the running state of every tile), 2 tile outputs

@@ -17,7 +17,8 @@
 //   k_fused_tiles  per (tile, batch): the summed log2-gate of the tile for every head (level 0 of
 //                  the block sums); clears the tiles' publication flags and the ticket counters
 //   k_fused_tree   per (b, h): aligned block sums of the tile totals, levels 1 .. J-1 (the decay
-//                  gaps between a tile and its source groups are sums of a few of them)
+//                  gaps between a tile and its source groups are sums of a few of them); not launched
+//                  where a tile sums the totals itself (kScanTiles)
 //   k_fused_fwd    per tile: the tile's state and node, the causal 128 x 128 masked contraction,
 //                  and the lambda-weighted terms of every inter-tile level from the published nodes
 //
@@ -50,6 +51,12 @@ namespace {
 
 constexpr uint64_t kSpinTicks = 500000;  // 5 ms of the 100 MHz real-time counter
 constexpr int kQueues = 8;               // XCDs of an MI355X
+// Sequences of at most this many tiles need no block sums: a wave holds the totals of all earlier tiles,
+// one per lane, and scans them.  (The backward reads the block sums, so a forward that leaves its
+// summaries forms them.)  Saves a launch of 3 to 5 us: 14.4 -> 11.6 us at B = 1, H = 8, T = 320, d = 64;
+// 23.5 -> 21.3 at B = 2, H = 8, T = 2048; 181.5 -> 180.2 at B = 4, H = 32, T = 8192.  One launch for the totals
+// and the block sums together (a workgroup per 16 heads) was slower from 8 tiles on.
+constexpr int64_t kScanTiles = 64;
 
 struct FusedWs {
   __bf16* node;    // [BH][N] node slots of DK * DV bf16, in the fragment-major MFMA result layout
@@ -256,8 +263,13 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_fused_fwd(
   if constexpr (HAS_LAMBDA) lds_copy_lambda<R, NT>(lam_s, lam, row0, H, h, L, nrow);
   lds_copy_rows<DK, R, NT>(k_s, k + (row0 * Hqk + hq) * DK, (int64_t)Hqk * DK, nrow);
   lds_copy_rows<DV, R, NT>(v_s, v + (row0 * H + h) * DV, (int64_t)H * DV, nrow);
-  float lb = 0.f;
-  if (lane < J && ((u >> lane) & 1)) lb = ws.bsum[bh * ws.stride + bsum_offset(N, lane) + (u >> lane) - 1];
+  const bool scan = !BWD_OUT && N <= kScanTiles;
+  float lb = 0.f;  // scan: lane x holds the total of tile u - 1 - x
+  if (scan) {
+    if (lane < u) lb = ws.bsum[bh * ws.stride + u - 1 - lane];
+  } else if (lane < J && ((u >> lane) & 1)) {
+    lb = ws.bsum[bh * ws.stride + bsum_offset(N, lane) + (u >> lane) - 1];
+  }
   auto slot_of = [&](int j) -> int64_t { return group_end(u, j) - 1; };  // node(e - 1) covers the group ending at e
   // the flags of all the tile's source groups in one poll (lane j - 1: level j); polled again after
   // the intra-tile phase, so that most levels need no poll of their own
@@ -274,8 +286,16 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_fused_fwd(
       if (r == 0) ws.t1[bh * N + u] = cl_s[R - 1];
     }
   }
-  // gap_j (lane j - 1): summed totals of the tile's lower-level source groups
-  const float gapv = wave_inclusive_scan(lb) - lb;
+  // gap_j (lane j - 1): summed totals of the tile's lower-level source groups, i.e. of the u % 2^(j-1)
+  // tiles before it
+  float gapv = wave_inclusive_scan(lb);
+  if (scan) {
+    const int m = u & ((1 << (lane < 8 ? lane : 8)) - 1);  // levels j - 1 < 6
+    const float sum = __shfl(gapv, m > 0 ? m - 1 : 0, 64);
+    gapv = m > 0 ? sum : 0.f;
+  } else {
+    gapv -= lb;
+  }
   wait_vmem();
   __syncthreads();  // K, V, lambda, decays visible
   frag qA[KS], qB[KS];
@@ -608,7 +628,7 @@ static hipError_t launch_fused(const Mamba2Args& a, hipStream_t st, hipEvent_t* 
   hipLaunchKernelGGL((k_fused_tiles<kFastRows>), dim3((unsigned)w.N, (unsigned)a.B), dim3(256), 0, st, a.log_alpha, ws,
                      a.T, (int)a.H, w.N);
   if (ev) (void)hipEventRecord(ev[1], st);
-  if (w.J > 1) {
+  if (w.J > 1 && (bwd_out || w.N > kScanTiles)) {
     const int64_t n1 = (w.N + 1) / 2;  // the largest level formed in LDS
     hipLaunchKernelGGL(k_fused_tree, dim3((unsigned)BH), dim3(256), (size_t)n1 * 2 * sizeof(float), st, ws, w.N, w.J);
   }
