@@ -7,6 +7,7 @@ fallback implementation.
 """
 
 import ctypes
+import functools
 import os
 
 # PyTorch ships its own HIP runtime under the same soname as ROCm's (libamdhip64.so.7).  Load it
@@ -100,6 +101,10 @@ def ll_num_levels(T: int) -> int:
     return lib.ll_num_levels(T)
 
 
+# ll_num_levels of a tensor's length, without a foreign call at each use
+_levels_of = functools.lru_cache(maxsize=256)(ll_num_levels)
+
+
 def ll_supported(variant: int, dtype: int, C: int, d_k: int, d_v: int) -> bool:
     return bool(lib.ll_supported(variant, dtype, C, d_k, d_v))
 
@@ -114,13 +119,10 @@ def ll_status_string(status: int) -> str:
 
 # ----------------------------------------------------------------------- torch-facing wrappers
 
-def _torch():
-    import torch
-    return torch
-
+# A call's checks and conversions take longer than the launch of a small kernel (a decoding step of a
+# few sequences, a short prompt's forward), so they read each attribute once and build no objects.
 
 def _dtype_code(t):
-    torch = _torch()
     if t.dtype == torch.float32:
         return LL_F32
     if t.dtype == torch.bfloat16:
@@ -129,29 +131,28 @@ def _dtype_code(t):
 
 
 def _check(t, name, dtype=None, shape=None):
-    torch = _torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # torch's current stream of the current device, without building a Stream object
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _prepare(variant, q, k, v, log_alpha, beta, lam, C, out, workspace, grouped=False):
-    torch = _torch()
     B, T, Hqk, dk = q.shape
     H = v.shape[2] if grouped else Hqk
     dv = v.shape[-1]
@@ -161,15 +162,16 @@ def _prepare(variant, q, k, v, log_alpha, beta, lam, C, out, workspace, grouped=
     _check(log_alpha, "log_alpha", torch.float32, (B, T, H))
     if beta is not None:
         _check(beta, "beta", torch.float32, (B, T, H))
-    L = ll_num_levels(T)
+    L = _levels_of(T)
     if lam is not None:
         _check(lam, "lambda", torch.float32, (B, T, H, L))
     code = _dtype_code(q)
     if out is None:
-        out = torch.empty((B, T, H, dv), dtype=q.dtype, device=q.device)
-    _check(out, "out", q.dtype, (B, T, H, dv))
-    need = ll_workspace_size(variant, code, B, T, H, dk, dv, C, lam is not None)
+        out = q.new_empty((B, T, H, dv))
+    else:
+        _check(out, "out", q.dtype, (B, T, H, dv))
     if workspace is None:
+        need = ll_workspace_size(variant, code, B, T, H, dk, dv, C, lam is not None)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
     _check(workspace, "workspace", torch.uint8)
     return (B, T, H, dk, dv, code), out, workspace
@@ -191,7 +193,6 @@ def ll_mamba2_fwd_noalloc(q, k, v, log_alpha, lam, C, out, stream=None):
     """ll_mamba2_fwd through the entry point that allocates nothing: the library works in its
     static per-GPU scratch, so calls on one GPU must be ordered.  `out` is caller-allocated.
     Returns `out`; raises LLError (LL_ERR_SCRATCH beyond LL_NOALLOC_SCRATCH_BYTES)."""
-    torch = _torch()
     B, T, H, dk = q.shape
     dv = v.shape[-1]
     _check(q, "q")
@@ -199,7 +200,7 @@ def ll_mamba2_fwd_noalloc(q, k, v, log_alpha, lam, C, out, stream=None):
     _check(v, "v", q.dtype, (B, T, H, dv))
     _check(log_alpha, "log_alpha", torch.float32, (B, T, H))
     if lam is not None:
-        _check(lam, "lambda", torch.float32, (B, T, H, ll_num_levels(T)))
+        _check(lam, "lambda", torch.float32, (B, T, H, _levels_of(T)))
     _check(out, "out", q.dtype, (B, T, H, dv))
     st = lib.ll_mamba2_fwd_noalloc(_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(lam), _ptr(out),
                                    B, T, H, dk, dv, C, _dtype_code(q), _stream(stream))
@@ -209,14 +210,13 @@ def ll_mamba2_fwd_noalloc(q, k, v, log_alpha, lam, C, out, stream=None):
 
 
 def _ml_call(q, k, v, log_alpha, Lam, C, out, workspace, stream, handles):
-    torch = _torch()
     B, T, H, dk = q.shape
     dv = v.shape[-1]
     _check(q, "q")
     _check(k, "k", q.dtype, (B, T, H, dk))
     _check(v, "v", q.dtype, (B, T, H, dv))
     _check(log_alpha, "log_alpha", torch.float32, (B, T, H))
-    L = ll_num_levels(T)
+    L = _levels_of(T)
     if Lam.dim() == 5:
         form = LL_LAMBDA_DIAG
         _check(Lam, "Lambda", torch.float32, (B, T, H, L, dk))
@@ -225,8 +225,9 @@ def _ml_call(q, k, v, log_alpha, Lam, C, out, workspace, stream, handles):
         _check(Lam, "Lambda", torch.float32, (B, T, H, L, dk, dk))
     code = _dtype_code(q)
     if out is None:
-        out = torch.empty((B, T, H, dv), dtype=q.dtype, device=q.device)
-    _check(out, "out", q.dtype, (B, T, H, dv))
+        out = q.new_empty((B, T, H, dv))
+    else:
+        _check(out, "out", q.dtype, (B, T, H, dv))
     if workspace is None:
         workspace = ll_mamba2_matrix_lambda_workspace(q, v, C, full=form == LL_LAMBDA_FULL)
     _check(workspace, "workspace", torch.uint8)
@@ -242,7 +243,6 @@ def _ml_call(q, k, v, log_alpha, Lam, C, out, workspace, stream, handles):
 def ll_mamba2_matrix_lambda_workspace(q, v, C, full=True):
     """A workspace for ll_mamba2_fwd_matrix_lambda shaped for q [B, T, H, d_k] and v [B, T, H, d_v]
     (full=True: for full matrices, which also serves diagonal ones)."""
-    torch = _torch()
     B, T, H, dk = q.shape
     form = LL_LAMBDA_FULL if full else LL_LAMBDA_DIAG
     need = lib.ll_mamba2_matrix_lambda_workspace_size(form, _dtype_code(q), B, T, H, dk, v.shape[-1], C)
@@ -284,7 +284,7 @@ def ll_decode_state_bytes(B, H, dk, dv, L):
 def ll_mamba2_decode_init(state, B, H, dk, dv, L, dtype, stream=None):
     """Resets `state` (a uint8 device tensor of ll_decode_state_bytes(...) bytes) to the empty
     sequence; `dtype` is the torch dtype of the per-token q, k, v, o."""
-    code = LL_BF16 if dtype == _torch().bfloat16 else LL_F32
+    code = LL_BF16 if dtype == torch.bfloat16 else LL_F32
     st = lib.ll_mamba2_decode_init(_ptr(state), state.numel(), B, H, dk, dv, L, code, _stream(stream))
     if st != LL_OK:
         raise LLError(st)
@@ -293,7 +293,6 @@ def ll_mamba2_decode_init(state, B, H, dk, dv, L, dtype, stream=None):
 def ll_mamba2_decode_step(q, k, v, log_alpha, lam, state, t, L, out=None, stream=None):
     """Feeds token t: q, k [B, H, d_k], v [B, H, d_v], log_alpha [B, H], lam [B, H, L] or None;
     returns o [B, H, d_v].  `state` is the uint8 device tensor set up by ll_mamba2_decode_init."""
-    torch = _torch()
     B, H, dk = q.shape
     dv = v.shape[-1]
     _check(q, "q")
@@ -304,8 +303,9 @@ def ll_mamba2_decode_step(q, k, v, log_alpha, lam, state, t, L, out=None, stream
         _check(lam, "lambda", torch.float32, (B, H, L))
     _check(state, "state", torch.uint8)
     if out is None:
-        out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
-    _check(out, "out", q.dtype, (B, H, dv))
+        out = q.new_empty((B, H, dv))
+    else:
+        _check(out, "out", q.dtype, (B, H, dv))
     st = lib.ll_mamba2_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(lam), _ptr(out), _ptr(state),
                                    state.numel(), t, B, H, dk, dv, L, _dtype_code(q), _stream(stream))
     if st != LL_OK:
@@ -315,7 +315,7 @@ def ll_mamba2_decode_step(q, k, v, log_alpha, lam, state, t, L, out=None, stream
 
 def ll_gdn_decode_init(state, B, H, dk, dv, L, dtype, stream=None):
     """Resets `state` for log-linear Gated DeltaNet decoding (same buffer as the Mamba-2 calls)."""
-    code = LL_BF16 if dtype == _torch().bfloat16 else LL_F32
+    code = LL_BF16 if dtype == torch.bfloat16 else LL_F32
     st = lib.ll_gdn_decode_init(_ptr(state), state.numel(), B, H, dk, dv, L, code, _stream(stream))
     if st != LL_OK:
         raise LLError(st)
@@ -324,7 +324,6 @@ def ll_gdn_decode_init(state, B, H, dk, dv, L, dtype, stream=None):
 def ll_gdn_decode_step(q, k, v, log_alpha, beta, lam, state, t, L, out=None, stream=None):
     """Feeds token t to log-linear Gated DeltaNet decoding: as ll_mamba2_decode_step plus
     beta [B, H] (float32, required)."""
-    torch = _torch()
     B, H, dk = q.shape
     dv = v.shape[-1]
     _check(q, "q")
@@ -336,8 +335,9 @@ def ll_gdn_decode_step(q, k, v, log_alpha, beta, lam, state, t, L, out=None, str
         _check(lam, "lambda", torch.float32, (B, H, L))
     _check(state, "state", torch.uint8)
     if out is None:
-        out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
-    _check(out, "out", q.dtype, (B, H, dv))
+        out = q.new_empty((B, H, dv))
+    else:
+        _check(out, "out", q.dtype, (B, H, dv))
     st = lib.ll_gdn_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(beta), _ptr(lam), _ptr(out),
                                 _ptr(state), state.numel(), t, B, H, dk, dv, L, _dtype_code(q), _stream(stream))
     if st != LL_OK:
@@ -347,7 +347,6 @@ def ll_gdn_decode_step(q, k, v, log_alpha, beta, lam, state, t, L, out=None, str
 
 def _event_handles(events, n, stream):
     """HIP event handles of `n` torch.cuda.Event objects (created with enable_timing=True)."""
-    torch = _torch()
     if len(events) != n:
         raise ValueError(f"events must hold {n} torch.cuda.Event objects")
     s = torch.cuda.current_stream() if stream is None else stream
@@ -377,7 +376,6 @@ def ll_mamba2_fwd_staged(q, k, v, log_alpha, lam, C, events, out=None, workspace
 
 
 def _bwd_call(q, k, v, log_alpha, lam, d_o, C, grads, workspace, stream, handles, after_fwd=False):
-    torch = _torch()
     B, T, Hqk, dk = q.shape
     H, dv = v.shape[2], v.shape[-1]
     _check(q, "q")
@@ -385,7 +383,7 @@ def _bwd_call(q, k, v, log_alpha, lam, d_o, C, grads, workspace, stream, handles
     _check(v, "v", q.dtype, (B, T, H, dv))
     _check(d_o, "d_o", q.dtype, (B, T, H, dv))
     _check(log_alpha, "log_alpha", torch.float32, (B, T, H))
-    L = ll_num_levels(T)
+    L = _levels_of(T)
     _check(lam, "lambda", torch.float32, (B, T, H, L))
     code = _dtype_code(q)
     if grads is None:
@@ -432,7 +430,6 @@ def ll_mamba2_bwd(q, k, v, log_alpha, lam, d_o, C, grads=None, workspace=None, s
 def ll_mamba2_bwd_workspace(q, v, C):
     """A workspace for the backward shaped for q [B, T, H_qk, d_k] and v [B, T, H, d_v] (also usable
     by the forward, which then leaves there the level summaries ll_mamba2_bwd_after_fwd reuses)."""
-    torch = _torch()
     B, T, Hqk, dk = q.shape
     need = lib.ll_mamba2_bwd_workspace_size(_dtype_code(q), B, T, v.shape[2], Hqk, dk, v.shape[-1], C)
     return torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
@@ -475,7 +472,6 @@ def ll_gdn_fwd_staged(q, k, v, log_alpha, beta, lam, C, events, out=None, worksp
 
 def ll_debug_level_map(T, C, stream=None):
     """The level map the kernels use, as a [T, T] int8 device tensor (-1 above the diagonal)."""
-    torch = _torch()
     out = torch.empty((T, T), dtype=torch.int8, device="cuda")
     st = lib.ll_debug_level_map(T, C, _ptr(out), _stream(stream))
     if st != LL_OK:
@@ -486,7 +482,6 @@ def ll_debug_level_map(T, C, stream=None):
 # ----------------------------------------------------------------------- autograd
 
 def _autograd_function():
-    torch = _torch()
 
     class LogLinearMamba2(torch.autograd.Function):
         """O = log-linear Mamba-2 attention of (q, k, v, log_alpha, lam) as a differentiable op: the
