@@ -131,13 +131,14 @@ __device__ inline int swz(int r, int c) {
 // waves in turn.  Rows at or beyond `nrow` are filled from row nrow - 1 (callers never read
 // them).  The copy is complete once the issuing wave has waited for its vector-memory operations.
 // AUX: cache-policy bits of the loads (0 by default; 2, non-temporal, for data read once).
+// The NT threads are waves 0 .. NT/64 - 1 of the workgroup, or `wave` is the wave's index among them.
 template <int D, int ROWS, int NT, int AUX = 0>
-__device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src, int64_t stride, int nrow) {
+__device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src, int64_t stride, int nrow,
+                                     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
   constexpr int CH = D / 8;      // chunks per row
   constexpr int RPI = NT / CH;   // rows per pass of all waves
   static_assert(NT % CH == 0 && RPI % CH == 0 && ROWS % RPI == 0, "whole rows per pass");
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q0 = wave * 64 + lane;                     // chunk position in the first pass
   const int r0 = q0 / CH, c = (q0 % CH) ^ (r0 & (CH - 1));  // the swizzle repeats every pass
 #pragma unroll
@@ -152,8 +153,8 @@ __device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src
 
 // bf16 MFMA operand fragment down the rows of a swizzled tile (as frag_down_rows).
 template <int D>
-__device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+__device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0, int lane = threadIdx.x & 63) {
+  const int g = lane >> 4, i = lane & 15;
   const int r = row0 + 4 * g + (i >> 2), col = col0 + 4 * (i & 3);
   const bf16x4 lo = lds_read_tr(m + swz<D>(r, col >> 3) + (col & 7));
   const bf16x4 hi = lds_read_tr(m + swz<D>(r + 16, col >> 3) + (col & 7));
@@ -163,9 +164,18 @@ __device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0)
 // bf16 MFMA operand fragment along a row of a swizzled tile: row row0 + (lane % 16), the 8
 // elements starting at column 8 * chunk0 + 8 * (lane / 16).
 template <int D>
-__device__ inline bf16x8 frag_along_row_swz(const __bf16* m, int row0, int chunk0) {
-  const int lane = threadIdx.x & 63;
+__device__ inline bf16x8 frag_along_row_swz(const __bf16* m, int row0, int chunk0, int lane = threadIdx.x & 63) {
   return *reinterpret_cast<const bf16x8*>(m + swz<D>(row0 + (lane & 15), chunk0 + (lane >> 4)));
+}
+
+// As frag_along_row_swz with the k slots in the order of frag_down_rows (and of two stacked 16 x 16
+// results): row row0 + (lane % 16), columns k0 + 4g + {0..3} (slots 0-3), k0 + 16 + 4g + {0..3} (4-7).
+template <int D>
+__device__ inline bf16x8 frag_along_row_perm(const __bf16* m, int row0, int k0, int lane = threadIdx.x & 63) {
+  const int g = lane >> 4, r = row0 + (lane & 15), c = (k0 >> 3) + (g >> 1);
+  const bf16x4 lo = *reinterpret_cast<const bf16x4*>(m + swz<D>(r, c) + 4 * (g & 1));
+  const bf16x4 hi = *reinterpret_cast<const bf16x4*>(m + swz<D>(r, c + 2) + 4 * (g & 1));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 // Copies n 16-byte pieces (n a multiple of 64) into LDS, piece q to dst + 16 q bytes, from global

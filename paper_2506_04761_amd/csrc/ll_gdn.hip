@@ -41,60 +41,7 @@ namespace ll {
 namespace gdn {
 
 constexpr int kMaxJ = 16;      // inter-chunk levels handled by the read-out (T <= C * 2^16)
-constexpr int kChunkWaves = 8; // waves per gdn_chunk workgroup
 typedef __bf16 bf;
-
-// Element offset of entry (r, k) of a staged bf16 matrix with rows of ld elements whose 8-element
-// chunks are XOR-swizzled by row group when SW: chunk k / 8 of row r sits at position
-// (k / 8) ^ ((r / 8) % 8).  Used for the transposed (d-major) copies of the chunk's K and V, whose
-// rows of C = 64 tokens are written eight rows at a time (see the staging in k_gdn_chunk).
-template <bool SW>
-__device__ inline int stg(int r, int ld, int k) {
-  return r * ld + (SW ? ((((k >> 3) ^ (r >> 3)) & 7) << 3) + (k & 7) : k);
-}
-
-// C = A B over 16x16 output tiles, A [M][K] row-major (lda), Bt = B^T [N][K] row-major (ldb), both
-// bf16 in LDS (SWA / SWB: the operand's chunks are swizzled as by stg, K = 64); tiles dealt
-// round-robin to the kChunkWaves waves; epi(mt, nt, acc) consumes each tile (lane holds column
-// 16 nt + (lane & 15), rows 16 mt + 4 (lane >> 4) + r).
-template <int M, int N, int K, bool SWA = false, bool SWB = false, typename Epi>
-__device__ inline void gemm_lds(const bf* A, int lda, const bf* Bt, int ldb, Epi epi) {
-  using MF = Mfma<bf>;
-  static_assert(!(SWA || SWB) || K == 64, "swizzled operands have rows of 64 elements");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, g = lane >> 4;
-  constexpr int MT = M / 16, NT = N / 16;
-  for (int tile = wave; tile < MT * NT; tile += kChunkWaves) {
-    const int mt = tile / NT, nt = tile % NT;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < K / MF::KSTEP; ++ks) {
-      const int k0 = ks * MF::KSTEP + g * MF::KPL;
-      acc = MF::mma(MF::load(&A[stg<SWA>(mt * 16 + r16, lda, k0)]), MF::load(&Bt[stg<SWB>(nt * 16 + r16, ldb, k0)]), acc);
-    }
-    epi(mt, nt, acc);
-  }
-}
-
-// As gemm_lds with the wave's tiles unrolled: epi(i, mt, nt, acc) for the wave's i-th tile
-// (tile wave + kChunkWaves i), so that the epilogue can index registers by i.
-template <int M, int N, int K, typename Epi>
-__device__ inline void gemm_lds_unrolled(const bf* A, int lda, const bf* Bt, int ldb, Epi epi) {
-  using MF = Mfma<bf>;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, g = lane >> 4;
-  constexpr int MT = M / 16, NT = N / 16;
-  static_assert(MT * NT % kChunkWaves == 0, "whole rounds of tiles");
-#pragma unroll
-  for (int i = 0; i < MT * NT / kChunkWaves; ++i) {
-    const int tile = wave + i * kChunkWaves, mt = tile / NT, nt = tile % NT;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < K / MF::KSTEP; ++ks) {
-      const int k0 = ks * MF::KSTEP + g * MF::KPL;
-      acc = MF::mma(MF::load(&A[(mt * 16 + r16) * lda + k0]), MF::load(&Bt[(nt * 16 + r16) * ldb + k0]), acc);
-    }
-    epi(i, mt, nt, acc);
-  }
-}
 
 // "kfrag" layout of a K x N bf16 matrix X (KR = K rows), in which X is read as the B operand of a
 // product Y X: the operand fragment of column tile nt and k step ks (32 rows) is 64 lanes x 8
@@ -107,362 +54,513 @@ __device__ inline int kfrag_idx(int k, int n) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 1: per-chunk WY solve and chunk-local products.  One workgroup (kChunkWaves waves) per chunk.
-// Outputs (workspace, per chunk): Qc [C][DK] bf16 row-major, P_z [DK][DK] bf16 (kfrag layout for
-// even chunks z, row-major for odd ones: the two sides of a tree combination), H_z [DK][DV] bf16
-// (kfrag), intra-chunk output [C][DV] fp32 in the MFMA result layout (16 x 16 tiles, row tile
-// major; lane l of a tile holds rows 4 (l / 16) + 0..3 of column l % 16).
+// Kernel 1: WY solve and products of a pair of chunks.  One workgroup of 8 waves per pair; half `hf`
+// (4 waves) takes chunk 2 zp + hf, wave w of a half its 16-row tile w.  Outputs (workspace): per chunk
+// Qc [C][DK] bf16 row-major (the query seen through its pair's transitions up to it) and the intra-pair
+// output [C][DV] fp32 in the MFMA result layout (16 x 16 tiles, row tile major; lane l of a tile holds
+// rows 4 (l / 16) + 0..3 of column l % 16); per pair P [DK][DK] bf16 (kfrag layout for even pairs,
+// row-major for odd ones: the two sides of a tree combination) and H [DK][DV] bf16 (kfrag).
+//
+// A pair's transition is that of 128 tokens, so that the tree and the read-out start at pairs: with
+// W_i, U_i the chunks' own WY factors and G = W_1 K~_0^T (64 x 64),
+//   W_1' = W_1 P_0 = gamma_0 W_1 - G W_0,   U_1' = U_1 - W_1 H_0 = U_1 - G U_0,
+// and the same for Q_1 (its product with H_0 being level log2 C + 1 of chunk 1's rows); then
+//   P = gamma_0 gamma_1 I - K~^T [W_0; W_1'],   H = K~^T [U_0; U_1'].
+// Against one chunk at a time this halves the nodes written and read and drops a tree level.
+//
+// Registers carry what one wave both makes and uses: a product formed transposed (rows 4g + r, columns
+// lane % 16) is, packed to bf16, an operand of the next one, its k slots in the order of
+// frag_down_rows.  LDS per half: K, Q, V (row-major, swizzled; direct loads), T_G, and the fp32 blocks of
+// L and of the inverse, whose room W takes after the inversion; U takes Q's.
 // ---------------------------------------------------------------------------------------------
-template <int C, int DK, int DV, bool HAS_LAMBDA>
-__global__ __launch_bounds__(64 * kChunkWaves) void k_gdn_chunk(const bf* __restrict__ q, const bf* __restrict__ k,
-                                                   const bf* __restrict__ v, const float* __restrict__ log_alpha,
-                                                   const float* __restrict__ beta, const float* __restrict__ lam,
-                                                   bf* __restrict__ qc_out, bf* __restrict__ pz_out,
-                                                   bf* __restrict__ hz_out, float* __restrict__ oin_out,
-                                                   int64_t Tlen, int H, int L, int64_t nchunks) {
-  static_assert(C == 64, "the inversion works on 4 x 4 blocks of 16 x 16 (one lane per column of wave 0)");
-  constexpr int LOG2C = 6;
-  constexpr int PD = 8;                 // row padding (elements)
-  constexpr int LDD = DK + PD;          // rows of length d_k
-  constexpr int LDC = C + PD;           // rows of length C
-  constexpr int VEC = 8;
-  constexpr int LDL = C + 4;            // fp32 L rows: 16-byte aligned, read four entries at a time
-  // region 1: phase A/B (K, Q row-major, fp32 L) reused in phase C/D (W^T, U^T, masked P)
-  constexpr int R1A = 2 * C * LDD * 2 + C * LDL * 4;
-  constexpr int R1B = (DK * LDC + DV * LDC + C * LDC) * 2;
-  constexpr int R1 = R1A > R1B ? R1A : R1B;
-  __shared__ __attribute__((aligned(16))) char r1[R1];
-  __shared__ bf kgt_s[DK * LDC];   // (gamma K)^T, chunks swizzled (stg)
-  __shared__ bf kdt_s[DK * LDC];   // (decay-to-end K)^T, chunks swizzled
-  __shared__ bf vt_s[DV * LDC];    // V^T, chunks swizzled
-  __shared__ bf pg_s[C * LDC];     // P_G
-  __shared__ bf z_s[C * LDC];      // T_G
-  __shared__ bf zt_s[C * LDC];     // T_G^T
-  __shared__ float cl_s[C], gm_s[C], dc_s[C], bt_s[C];
-  __shared__ float lam_s[HAS_LAMBDA ? C * (LOG2C + 1) : 1];
-  __shared__ float xs_s[10 * 256];  // fp32 blocks (i, j), j <= i, of X = (I + L)^{-1}: block i(i+1)/2 + j
-  bf* k_s = reinterpret_cast<bf*>(r1);
-  bf* q_s = k_s + C * LDD;
-  float* l_s = reinterpret_cast<float*>(r1 + 2 * C * LDD * 2);
-  bf* wt_s = reinterpret_cast<bf*>(r1);
-  bf* ut_s = wt_s + DK * LDC;
-  bf* ph_s = ut_s + DV * LDC;
+template <int DK, int DV>
+struct PairHalf {  // LDS of one half
+  static constexpr int C = 64;
+  __attribute__((aligned(16))) bf k[C * DK];
+  __attribute__((aligned(16))) bf q[C * (DK > DV ? DK : DV)];  // Q, then U (own rows of each wave)
+  __attribute__((aligned(16))) bf v[C * DV];
+  __attribute__((aligned(16))) bf z[C * C];                    // T_G, row-major swizzled
+  union {
+    __attribute__((aligned(16))) float lx[2][10 * 256];        // blocks (i, j), j <= i, of L and of (I + L)^-1
+    __attribute__((aligned(16))) bf w[C * DK];                 // W
+  };
+  float cl[C], gm[C], dc[C], bt[C];  // cumulative log2-gates, exp2 of them, decay to the chunk's end, beta
+};
 
-  const int64_t N = Tlen / C;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
+// Two 16 x 16 results packed to bf16 (lane: rows 4g .. 4g + 3 of column lane % 16), joined to 16-byte pieces:
+// lanes of even g receive rows 4g .. 4g + 7 of x, lanes of odd g rows 4(g - 1) .. 4g + 3 of y, so that
+// each lane stores one whole piece (8-byte stores halve the lines a store instruction completes).
+__device__ inline bf16x8 pair_rows(bf16x4 x, bf16x4 y) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x2 a = __builtin_bit_cast(u32x2, x), b = __builtin_bit_cast(u32x2, y);
+  const auto p0 = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto p1 = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return __builtin_bit_cast(bf16x8, u32x4{p0[0], p1[0], p0[1], p1[1]});
+}
 
-  // A persistent grid: the workgroup takes chunks blockIdx.x, blockIdx.x + gridDim.x, ... (logical
-  // order (b, h, z) through the XCD mapping), and loads the next chunk's inputs (K, Q, V rows, gates,
-  // beta, lambda) into registers as soon as the current chunk has staged its own, so that their
-  // memory latency overlaps the current chunk's work.  A wave instruction loads 16-byte pieces of
-  // 8 tokens x 8 consecutive pieces (piece p of the tensor: token 8 (b % 8) + (l % 8), columns
-  // 8 (8 (b / 8) + l / 8) .. + 7, with b = p / 64 and l = p % 64): whole 128-byte lines, and in the
-  // transposed LDS copies eight rows 8 apart whose swizzled chunks fall in distinct banks.
-  constexpr int NTH = 64 * kChunkWaves;
-  constexpr int NKQ = C * DK / VEC / NTH, NVV = C * DV / VEC / NTH;  // 16-byte pieces per thread
-  static_assert(C == 64, "pieces of 8 tokens x 8 column pieces");
-  auto piece_t = [&](int p) { return ((p >> 6) & 7) * 8 + (p & 7); };        // token of piece p
-  auto piece_d = [&](int p) { return (((p >> 6) >> 3) * 8 + ((p & 63) >> 3)) * VEC; };  // first column
-  constexpr int NLW = HAS_LAMBDA ? (C * (LOG2C + 1) + NTH - 1) / NTH : 1;  // lambda values per thread
-  static_assert(C * DK / VEC % NTH == 0 && C * DV / VEC % NTH == 0, "whole passes of the workgroup");
-  bf16x8 kpre[NKQ], qpre[NKQ], vpre[NVV];
-  float la_r = 0.f, bt_r = 0.f, lam_r[NLW];
-  auto load_inputs = [&](int64_t it) {
-    const int64_t wk = xcd_remap(it, nchunks);
-    const int64_t zz = wk % N, bhh = wk / N;
-    const int hh = (int)(bhh % H), bb = (int)(bhh / H);
-    const int64_t t0 = (int64_t)bb * Tlen + zz * C;
-    // the small loads first and unconditionally (every wave, clamped indices; only wave 0 and the
-    // in-range entries are used), so that no wave waits on them where their registers are reused
-    la_r = log_alpha[(t0 + lane) * H + hh];  // scaled at its use: nothing waits for the load here
-    bt_r = beta[(t0 + lane) * H + hh];
+// Entry (r, c) of a 16 x 16 fp32 block whose 4-entry pieces are XOR-swizzled by row.
+__device__ inline int blk_at(int r, int c) { return r * 16 + ((((c >> 2) ^ (r >> 1)) & 3) << 2) + (c & 3); }
+__device__ inline int blk(int i, int j) { return (i * (i + 1) / 2 + j) * 256; }
+
+template <int DK, int DV, bool HAS_LAMBDA>
+__global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, const bf* __restrict__ k,
+                                                     const bf* __restrict__ v, const float* __restrict__ log_alpha,
+                                                     const float* __restrict__ beta, const float* __restrict__ lam,
+                                                     bf* __restrict__ qc_out, bf* __restrict__ pz_out,
+                                                     bf* __restrict__ hz_out, float* __restrict__ oin_out,
+                                                     int64_t Tlen, int H, int L, int64_t npairs) {
+  using M = Mfma<bf>;
+  typedef M::frag frag;
+  constexpr int C = 64, KS = DK / 32, KT = DK / 16, VT = DV / 16, NL = 8;  // NL: levels inside a pair
+  static_assert(DK == DV, "U takes Q's place");
+  __shared__ PairHalf<DK, DV> half_s[2];
+  __shared__ float lam_s[HAS_LAMBDA ? 2 * C * NL : 1];
+
+  const int64_t N = Tlen / C, N2 = (N + 1) / 2;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hf = wave >> 2, w = wave & 3;
+  PairHalf<DK, DV>&S = half_s[hf], &S0 = half_s[0], &S1 = half_s[1];
+  bf* k_s = S.k;
+  bf* z_s = S.z;
+  float *l_s = S.lx[0], *x_s = S.lx[1];
+  float* lam_h = lam_s + (HAS_LAMBDA ? hf * C * NL : 0);
+  auto zero4 = [] { return f32x4{0.f, 0.f, 0.f, 0.f}; };
+  auto pack = [](f32x4 x) {
+    bf16x4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = static_cast<bf>(x[r]);
+    return y;
+  };
+  auto join = [](bf16x4 lo, bf16x4 hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); };
+
+  // A persistent grid (one workgroup per CU, whose LDS allows no second): pairs blockIdx.x,
+  // blockIdx.x + gridDim.x, .. in logical order (b, h, pair); the next pair's inputs are loaded into
+  // registers while the last products of the current one run.
+  struct Where {
+    int64_t zp, bh, tok0;
+    int h;
+    bool valid;  // this half's chunk exists
+  };
+  auto where = [&](int64_t it) {
+    Where x;
+    const int64_t work = xcd_remap(it, npairs);
+    x.zp = work % N2;
+    x.bh = work / N2;
+    x.h = (int)(x.bh % H);
+    // a sequence of an odd number of chunks: the last pair's second chunk repeats the first one's
+    // rows with beta = 0 and no decay (no effect), and stores nothing
+    x.valid = 2 * x.zp + hf < N;
+    x.tok0 = (x.bh / H) * Tlen + (2 * x.zp + (x.valid ? hf : 0)) * C;
+    return x;
+  };
+  constexpr int CH = DK / 8, PCS = C * CH / 256, NLW = HAS_LAMBDA ? C * NL / 256 : 1;
+  bf16x8 kpre[PCS], qpre[PCS], vpre[PCS];  // piece (tid % 256) + 256 e: row piece / CH, 8 columns
+  float la_r, bt_r, lam_r[NLW];
+  auto load_inputs = [&](const Where& x, int tid) {
+    la_r = log_alpha[(x.tok0 + (tid & 63)) * H + x.h];
+    bt_r = beta[(x.tok0 + (tid & 63)) * H + x.h];
     if constexpr (HAS_LAMBDA) {
 #pragma unroll
       for (int e = 0; e < NLW; ++e) {
-        const int idx = tid + e * NTH, ic = idx < C * (LOG2C + 1) ? idx : C * (LOG2C + 1) - 1;
-        lam_r[e] = lam[((t0 + ic / (LOG2C + 1)) * H + hh) * L + ic % (LOG2C + 1)];
+        const int y = (tid & 255) + 256 * e, l = y % NL;
+        lam_r[e] = lam[((x.tok0 + y / NL) * H + x.h) * L + (l < L ? l : L - 1)];
       }
     }
 #pragma unroll
-    for (int e = 0; e < NKQ; ++e) {
-      const int idx = tid + e * NTH, t = piece_t(idx), d0 = piece_d(idx);
-      kpre[e] = *reinterpret_cast<const bf16x8*>(k + ((t0 + t) * H + hh) * DK + d0);
+    for (int e = 0; e < PCS; ++e) {
+      const int y = (tid & 255) + 256 * e;
+      const int64_t at = ((x.tok0 + y / CH) * H + x.h) * DK + 8 * (y % CH);
+      kpre[e] = *reinterpret_cast<const bf16x8*>(k + at);
+      qpre[e] = *reinterpret_cast<const bf16x8*>(q + at);
+      vpre[e] = *reinterpret_cast<const bf16x8*>(v + at);
     }
   };
-  // Q is prefetched in phase C
-  auto load_q = [&](int64_t it) {
-    const int64_t wk = xcd_remap(it, nchunks);
-    const int64_t zz = wk % N, bhh = wk / N;
-    const int hh = (int)(bhh % H), bb = (int)(bhh / H);
-    const int64_t t0 = (int64_t)bb * Tlen + zz * C;
+  Where cur = where(blockIdx.x);
+  load_inputs(cur, threadIdx.x);
+  for (int64_t it = blockIdx.x; it < npairs; it += gridDim.x) {
+  // opaque in every turn: the compiler would otherwise form the many lane-dependent LDS addresses of
+  // the body before the loop and spill them
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int64_t zp = cur.zp, bh = cur.bh;
+  const bool valid = cur.valid;
+  const int64_t cidx = bh * N + 2 * zp + hf;
+  if (it != (int64_t)blockIdx.x) __syncthreads();  // the previous pair's readers of LDS are done
 #pragma unroll
-    for (int e = 0; e < NKQ; ++e) {
-      const int idx = tid + e * NTH, t = piece_t(idx), d0 = piece_d(idx);
-      qpre[e] = *reinterpret_cast<const bf16x8*>(q + ((t0 + t) * H + hh) * DK + d0);
-    }
-  };
-  // V is prefetched separately, later in the chunk (phase B), so that no wave issues the whole
-  // burst at once
-  auto load_v = [&](int64_t it) {
-    const int64_t wk = xcd_remap(it, nchunks);
-    const int64_t zz = wk % N, bhh = wk / N;
-    const int hh = (int)(bhh % H), bb = (int)(bhh / H);
-    const int64_t t0 = (int64_t)bb * Tlen + zz * C;
-#pragma unroll
-    for (int e = 0; e < NVV; ++e) {
-      const int idx = tid + e * NTH, t = piece_t(idx), d0 = piece_d(idx);
-      vpre[e] = *reinterpret_cast<const bf16x8*>(v + ((t0 + t) * H + hh) * DV + d0);
-    }
-  };
-  if (blockIdx.x < nchunks) {
-    load_inputs(blockIdx.x);
-    load_v(blockIdx.x);
-    load_q(blockIdx.x);
-  }
-  // The first chunk's inputs are awaited here, once: the compiler's counter waits at the loop head
-  // then see, on every path into it, the epilogue stores issued after the prefetch, and no longer
-  // wait for those stores to drain before each chunk's first use of its prefetched inputs.
-  wait_vmem();
-  for (int64_t it = blockIdx.x; it < nchunks; it += gridDim.x) {
-  const int64_t work = xcd_remap(it, nchunks);  // (b, h, z)
-  const int64_t z = work % N;
-  const int64_t bh = work / N;
-  const int h = (int)(bh % H), b = (int)(bh / H);
-  const int64_t tok0 = (int64_t)b * Tlen + z * C;
-  const int64_t cidx = bh * N + z;
-  __syncthreads();  // the previous chunk's readers of LDS are done
-
-  // ---- phase A: gates, staging, K K^T and Q K^T
-  if (wave == 0) {
-    const float la = lane < C ? la_r * kLog2e : 0.f;
-    const float cl = wave_inclusive_scan(la);
-    const float tot = __shfl(cl, C - 1, 64);
-    if (lane < C) {
-      cl_s[lane] = cl;
-      gm_s[lane] = fast_exp2(cl);
-      dc_s[lane] = fast_exp2(tot - cl);
-      bt_s[lane] = bt_r;
-    }
+  for (int e = 0; e < PCS; ++e) {
+    const int y = (tid & 255) + 256 * e, at = swz<DK>(y / CH, y % CH);
+    *reinterpret_cast<bf16x8*>(S.k + at) = kpre[e];
+    *reinterpret_cast<bf16x8*>(S.q + at) = qpre[e];
+    *reinterpret_cast<bf16x8*>(S.v + at) = vpre[e];
   }
   if constexpr (HAS_LAMBDA) {
 #pragma unroll
-    for (int e = 0; e < NLW; ++e) {
-      const int idx = tid + e * NTH;
-      if (idx < C * (LOG2C + 1)) lam_s[idx] = lam_r[e];
-    }
+    for (int e = 0; e < NLW; ++e) lam_h[(tid & 255) + 256 * e] = lam_r[e];
   }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < NKQ; ++e) {
-    const int idx = tid + e * NTH, t = piece_t(idx), d0 = piece_d(idx);
-    const bf16x8 kv = kpre[e], qv = qpre[e];
-    *reinterpret_cast<bf16x8*>(&k_s[t * LDD + d0]) = kv;
-    *reinterpret_cast<bf16x8*>(&q_s[t * LDD + d0]) = qv;
-    const float gt = gm_s[t], dt = dc_s[t];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const float x = static_cast<float>(kv[e]);
-      kgt_s[stg<true>(d0 + e, LDC, t)] = static_cast<bf>(x * gt);
-      kdt_s[stg<true>(d0 + e, LDC, t)] = static_cast<bf>(x * dt);
-    }
+  if (w == 0) {
+    const float cl = wave_inclusive_scan(valid ? la_r * kLog2e : 0.f);
+    const float tot = __shfl(cl, C - 1, 64);
+    S.cl[lane] = cl;
+    S.gm[lane] = fast_exp2(cl);
+    S.dc[lane] = fast_exp2(tot - cl);
+    S.bt[lane] = valid ? bt_r : 0.f;
   }
-#pragma unroll
-  for (int e = 0; e < NVV; ++e) {
-    const int idx = tid + e * NTH, t = piece_t(idx), d0 = piece_d(idx);
-    const bf16x8 vv = vpre[e];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) vt_s[stg<true>(d0 + e, LDC, t)] = vv[e];
-  }
-  if (it + gridDim.x < nchunks) load_inputs(it + gridDim.x);  // the next chunk's, while this one runs
-  __syncthreads();
-  // the Q entries of this lane's tiles of the corrected-query product (formed transposed: tile
-  // (mt, nt) holds columns d = 16 mt + 4 g + 0..3 of row t = 16 nt + (lane & 15)), read while Q is
-  // staged (its LDS region is reused by phase C), so that the product's epilogue issues no loads
-  constexpr int QCT = (DK / 16) * (C / 16) / kChunkWaves;
-  bf16x4 qreg[QCT];
-#pragma unroll
-  for (int i = 0; i < QCT; ++i) {
-    const int tile = wave + i * kChunkWaves, mt = tile / (C / 16), nt = tile % (C / 16);
-    qreg[i] = *reinterpret_cast<const bf16x4*>(&q_s[(nt * 16 + r16) * LDD + mt * 16 + 4 * g]);
-  }
-  // L[t][s] = beta_t (k_t . k_s) Gamma[t,s] for s < t (fp32);  P_G[t][s] = (q_t . k_s) Gamma[t,s], s <= t
-  gemm_lds<C, C, DK>(k_s, LDD, k_s, LDD, [&](int mt, int nt, f32x4 acc) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int t = mt * 16 + 4 * g + r, s = nt * 16 + r16;
-      l_s[t * LDL + s] = s < t ? bt_s[t] * acc[r] * fast_exp2(cl_s[t] - cl_s[s]) : 0.f;
-    }
-  });
   __syncthreads();
 
-  // ---- phase B: X = (I + L)^{-1} in 16 x 16 blocks (fp32), T_G = X diag(beta) into z_s[t][c] and
-  //      zt_s[c][t].  B1: wave 0 inverts the four diagonal blocks by forward substitution (lane
-  //      16 b + c = column c of block b) while the other waves form P_G and zero the blocks above
-  //      the diagonal.  B2: block row i = 1, 2, 3 in turn, X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj,
-  //      tile (i, j) on wave j (fp32 MFMA).
-  auto blk = [](int i, int j) { return (i * (i + 1) / 2 + j) * 256; };
-  auto put_t = [&](int t, int c, float x) {  // T_G entry (t, c)
-    const bf zv = static_cast<bf>(x * bt_s[c]);
-    z_s[t * LDC + c] = zv;
-    zt_s[c * LDC + t] = zv;
+  // ---- L[t][s] = beta_t (k_t . k_s) Gamma[t,s], s < t: the wave's diagonal block and some of the others
+  auto form_l = [&](int i, int j) {
+    f32x4 acc = zero4();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = M::mma(frag_along_row_swz<DK>(k_s, 16 * i, 4 * ks, lane), frag_along_row_swz<DK>(k_s, 16 * j, 4 * ks, lane), acc);
+    const int s = 16 * j + r16;
+    const float cs = S.cl[s];
+    const f32x4 bt = *reinterpret_cast<const f32x4*>(&S.bt[16 * i + 4 * g]);
+    const f32x4 ct = *reinterpret_cast<const f32x4*>(&S.cl[16 * i + 4 * g]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float y = bt[r] * acc[r] * fast_exp2(fminf(ct[r] - cs, 0.f));
+      l_s[blk(i, j) + blk_at(4 * g + r, r16)] = s < 16 * i + 4 * g + r ? y : 0.f;
+    }
   };
-  const bool more = it + gridDim.x < nchunks;
-  if (wave != 0) {
-    if (more) load_v(it + gridDim.x);
-    // P_G[t][s] = (q_t . k_s) Gamma[t,s], s <= t, 16 x 16 tiles dealt to the other waves
-    using MF = Mfma<bf>;
-    constexpr int MT = C / 16;
-    for (int tile = wave - 1; tile < MT * MT; tile += kChunkWaves - 1) {
-      const int mt = tile / MT, nt = tile % MT;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < DK / MF::KSTEP; ++ks) {
-        const int k0 = ks * MF::KSTEP + g * MF::KPL;
-        acc = MF::mma(MF::load(&q_s[(mt * 16 + r16) * LDD + k0]), MF::load(&k_s[(nt * 16 + r16) * LDD + k0]), acc);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = mt * 16 + 4 * g + r, s = nt * 16 + r16;
-        pg_s[t * LDC + s] = static_cast<bf>(s <= t ? acc[r] * fast_exp2(cl_s[t] - cl_s[s]) : 0.f);
-      }
-    }
-    // zeros above the diagonal blocks (rows of block i, columns of block j > i)
-    for (int idx = tid - 64; idx < 6 * 256; idx += 64 * (kChunkWaves - 1)) {
-      const int bj = idx >> 8, e = idx & 255;
-      const int bi = bj < 3 ? 0 : (bj < 5 ? 1 : 2);                // (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-      const int bc = bj < 3 ? bj + 1 : (bj < 5 ? bj - 1 : 3);
-      const int t = 16 * bi + (e >> 4), c = 16 * bc + (e & 15);
-      z_s[t * LDC + c] = static_cast<bf>(0.f);
-      zt_s[c * LDC + t] = static_cast<bf>(0.f);
-    }
-  } else {
-    const int bb = lane >> 4, c = lane & 15;
-    const float* lb = l_s + 16 * bb * LDL + 16 * bb;  // diagonal block bb of L
+  form_l(w, w);
+  if (w == 0) { form_l(1, 0); form_l(2, 0); }
+  if (w == 1) { form_l(2, 1); form_l(3, 0); }
+  if (w == 2) form_l(3, 1);
+  if (w == 3) form_l(3, 2);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  // ---- X = (I + L)^-1 in 16 x 16 blocks (fp32), T_G = X diag(beta).  Each wave inverts its diagonal block by
+  //      forward substitution (lane c of every 16: column c), then the blocks (1,0) and (3,2), then the
+  //      32 x 32 block below: X_21 = -X_22 (L_21 X_11) in halves of 32 rows.
+  auto put_z = [&](int t, int c, float x) { z_s[swz<C>(t, c >> 3) + (c & 7)] = static_cast<bf>(x * S.bt[c]); };
+  {
+    const float* lb = l_s + blk(w, w);
     float x[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+      f32x4 a = zero4();
 #pragma unroll
-      for (int j = 0; j + 3 < i; j += 4) {
-        const f32x4 lv = *reinterpret_cast<const f32x4*>(&lb[i * LDL + j]);  // broadcast per block
-        a0 += lv[0] * x[j];
-        a1 += lv[1] * x[j + 1];
-        a2 += lv[2] * x[j + 2];
-        a3 += lv[3] * x[j + 3];
+      for (int j = 0; j < i; j += 4) {
+        const f32x4 lv = *reinterpret_cast<const f32x4*>(&lb[blk_at(i, j)]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j + e < i) a[e] += lv[e] * x[j + e];
       }
-#pragma unroll
-      for (int j = i & ~3; j < i; ++j) a0 += lb[i * LDL + j] * x[j];
-      const float acc = ((i == c) ? 1.f : 0.f) - ((a0 + a1) + (a2 + a3));
-      x[i] = (i < c) ? 0.f : acc;
+      const float acc = ((i == r16) ? 1.f : 0.f) - ((a[0] + a[1]) + (a[2] + a[3]));
+      x[i] = (i < r16) ? 0.f : acc;
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      xs_s[blk(bb, bb) + i * 16 + c] = x[i];
-      put_t(16 * bb + i, 16 * bb + c, x[i]);
-    }
-    if (more) load_v(it + gridDim.x);
-  }
-  for (int i = 1; i < C / 16; ++i) {
-    __syncthreads();  // blocks of rows < i (and the diagonal ones) are in xs_s
-    if (wave < i) {
-      using MF = Mfma<float>;
-      const int jb = wave;
-      // Y = sum_{k=j}^{i-1} L_ik X_kj  (k slot 4 kk + g)
-      f32x4 y = {0.f, 0.f, 0.f, 0.f};
-      for (int kb = jb; kb < i; ++kb) {
-        const float* xb = xs_s + blk(kb, jb);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          y = MF::mma(l_s[(16 * i + r16) * LDL + 16 * kb + 4 * kk + g], xb[(4 * kk + g) * 16 + r16], y);
-      }
-      // X_ij = -X_ii Y  (k slot 4 g + r: Y in the result layout is the B operand directly)
-      const float* di = xs_s + blk(i, i);
-      f32x4 xv = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) xv = MF::mma(di[r16 * 16 + 4 * g + r], y[r], xv);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float xr = -xv[r];
-        xs_s[blk(i, jb) + (4 * g + r) * 16 + r16] = xr;
-        put_t(16 * i + 4 * g + r, 16 * jb + r16, xr);
-      }
+    for (int i = 0; i < 16; i += 4) {  // lane group g stores rows i + g
+      const float y0 = x[i], y1 = x[i + 1], y2 = x[i + 2], y3 = x[i + 3];
+      const float y = g & 2 ? (g & 1 ? y3 : y2) : (g & 1 ? y1 : y0);
+      x_s[blk(w, w) + blk_at(i + g, r16)] = y;
+      put_z(16 * w + i + g, 16 * w + r16, y);
     }
   }
+  if (!(w & 1))  // zeros of T_G that its products read: blocks (0, 1) and (2, 3)
+    *reinterpret_cast<bf16x4*>(z_s + swz<C>(16 * w + r16, 2 * (w + 1) + (g >> 1)) + 4 * (g & 1)) = pack(zero4());
   __syncthreads();
-
-  // ---- phase C: W = T_G (gamma K), U = T_G V (stored transposed), A_c = P_G T_G masked by M^H
-  if (more) load_q(it + gridDim.x);
-  gemm_lds<C, DK, C, false, true>(z_s, LDC, kgt_s, LDC, [&](int mt, int nt, f32x4 acc) {
-    bf16x4 w4;
+  using MF = Mfma<float>;
+  // acc += L_ik X_kj: k slot 4 kk + g
+  auto lx_mul = [&](int i, int kb, int j, f32x4 acc) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) w4[r] = static_cast<bf>(acc[r]);
-    *reinterpret_cast<bf16x4*>(&wt_s[(nt * 16 + r16) * LDC + mt * 16 + 4 * g]) = w4;
-  });
-  gemm_lds<C, DV, C, false, true>(z_s, LDC, vt_s, LDC, [&](int mt, int nt, f32x4 acc) {
-    bf16x4 u4;
+    for (int kk = 0; kk < 4; ++kk)
+      acc = MF::mma(l_s[blk(i, kb) + blk_at(r16, 4 * kk + g)], x_s[blk(kb, j) + blk_at(4 * kk + g, r16)], acc);
+    return acc;
+  };
+  // acc += X_ik Y, Y in the result layout (the B operand with k slot 4 g + r)
+  auto xy_mul = [&](int i, int kb, f32x4 y, f32x4 acc) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) u4[r] = static_cast<bf>(acc[r]);
-    *reinterpret_cast<bf16x4*>(&ut_s[(nt * 16 + r16) * LDC + mt * 16 + 4 * g]) = u4;
-  });
-  gemm_lds<C, C, C>(pg_s, LDC, zt_s, LDC, [&](int mt, int nt, f32x4 acc) {
+    for (int r = 0; r < 4; ++r) acc = MF::mma(x_s[blk(i, kb) + blk_at(r16, 4 * g + r)], y[r], acc);
+    return acc;
+  };
+  if (!(w & 1)) {
+    const f32x4 x = xy_mul(w + 1, w + 1, lx_mul(w + 1, w, w, zero4()), zero4());
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int t = mt * 16 + 4 * g + r, s = nt * 16 + r16;
-      float w = s <= t ? acc[r] : 0.f;
-      if constexpr (HAS_LAMBDA) w *= lam_s[t * (LOG2C + 1) + level_local(t, s)];
-      ph_s[t * LDC + s] = static_cast<bf>(w);
+      x_s[blk(w + 1, w) + blk_at(4 * g + r, r16)] = -x[r];
+      put_z(16 * (w + 1) + 4 * g + r, 16 * w + r16, -x[r]);
     }
-  });
-  __syncthreads();
-
-  // ---- phase D: intra output, corrected queries, transition and chunk state
-  // the intra output in the MFMA result layout, tile by tile (one 1 KB store per tile; the
-  // read-out kernel adds it to accumulators of the same layout)
-  float* oin = oin_out + cidx * (C * DV);
-  gemm_lds<C, DV, C, false, true>(ph_s, LDC, vt_s, LDC, [&](int mt, int nt, f32x4 acc) {
-    *reinterpret_cast<f32x4*>(oin + ((mt * (DV / 16) + nt) * 64 + lane) * 4) = acc;
-  });
-  bf* qc = qc_out + cidx * (C * DK);
-  // Qc^T = gamma Q^T - W^T P_G^T: four consecutive columns of one row of Qc per lane, one 8-byte
-  // store each
-  gemm_lds_unrolled<DK, C, C>(wt_s, LDC, pg_s, LDC, [&](int i, int mt, int nt, f32x4 acc) {
-    const int d0 = mt * 16 + 4 * g, t = nt * 16 + r16;
-    const float gt = gm_s[t];
-    bf16x4 q4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) q4[r] = static_cast<bf>(gt * static_cast<float>(qreg[i][r]) - acc[r]);
-    *reinterpret_cast<bf16x4*>(qc + t * DK + d0) = q4;
-  });
-  bf* pz = pz_out + cidx * (DK * DK);
-  const float gC = gm_s[C - 1];
-  // P_z = gamma_C I - K~^T W, stored four consecutive elements per lane: an even chunk's in the
-  // kfrag layout (rows d .. d + 3 of column e), an odd chunk's row-major from the transposed
-  // product (columns e .. e + 3 of row d)
-  if (!(z & 1)) {
-    gemm_lds<DK, DK, C, true, false>(kdt_s, LDC, wt_s, LDC, [&](int mt, int nt, f32x4 acc) {
-      const int d0 = mt * 16 + 4 * g, e = nt * 16 + r16;
-      bf16x4 p4;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) p4[r] = static_cast<bf>((d0 + r == e ? gC : 0.f) - acc[r]);
-      *reinterpret_cast<bf16x4*>(pz + kfrag_idx<DK>(d0, e)) = p4;
-    });
-  } else {
-    gemm_lds<DK, DK, C, false, true>(wt_s, LDC, kdt_s, LDC, [&](int mt, int nt, f32x4 acc) {
-      const int e0 = mt * 16 + 4 * g, d = nt * 16 + r16;
-      bf16x4 p4;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) p4[r] = static_cast<bf>((d == e0 + r ? gC : 0.f) - acc[r]);
-      *reinterpret_cast<bf16x4*>(pz + d * DK + e0) = p4;
-    });
   }
-  bf* hz = hz_out + cidx * (DK * DV);
-  gemm_lds<DK, DV, C, true, false>(kdt_s, LDC, ut_s, LDC, [&](int mt, int nt, f32x4 acc) {
-    bf16x4 h4;
+  __syncthreads();
+  {
+    const int i = 2 + (w >> 1), j = w & 1;
+    f32x4 y2 = lx_mul(2, 1, j, zero4());
+    if (j == 0) y2 = lx_mul(2, 0, 0, y2);
+    f32x4 x = xy_mul(i, 2, y2, zero4());
+    if (i == 3) {
+      f32x4 y3 = lx_mul(3, 1, j, zero4());
+      if (j == 0) y3 = lx_mul(3, 0, 0, y3);
+      x = xy_mul(3, 3, y3, x);
+    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) h4[r] = static_cast<bf>(acc[r]);
-    *reinterpret_cast<bf16x4*>(hz + kfrag_idx<DK>(mt * 16 + 4 * g, nt * 16 + r16)) = h4;
-  });
-  }  // chunk loop
+    for (int r = 0; r < 4; ++r) put_z(16 * i + 4 * g + r, 16 * j + r16, -x[r]);
+  }
+  __syncthreads();  // T_G complete; L and X free for W
+
+  const int t_own = 16 * w + r16;  // the wave's row of this lane (columns of the transposed products)
+  // ---- P_G^T (rows s, columns t): operand fragments pg (k = s)
+  frag pg[2];
+  {
+    frag qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_along_row_swz<DK>(S.q, 16 * w, 4 * ks, lane);
+    const float ct = S.cl[t_own];
+    bf16x4 p4[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      f32x4 acc = zero4();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) acc = M::mma(frag_along_row_swz<DK>(k_s, 16 * st, 4 * ks, lane), qf[ks], acc);
+      const f32x4 cs = *reinterpret_cast<const f32x4*>(&S.cl[16 * st + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float y = acc[r] * fast_exp2(fminf(ct - cs[r], 0.f));
+        acc[r] = 16 * st + 4 * g + r <= t_own ? y : 0.f;
+      }
+      p4[st] = pack(acc);
+    }
+    pg[0] = join(p4[0], p4[1]);
+    pg[1] = join(p4[2], p4[3]);
+  }
+  // ---- W^T = (K gamma)^T T_G^T and U^T = V^T T_G^T (columns t): W to LDS, both kept
+  bf16x4 wreg[KT];
+  f32x4 ureg[VT];
+  {
+    frag zf[2], zg[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      zf[ks] = frag_along_row_perm<C>(z_s, 16 * w, 32 * ks, lane);
+      const f32x4 g0 = *reinterpret_cast<const f32x4*>(&S.gm[32 * ks + 4 * g]);
+      const f32x4 g1 = *reinterpret_cast<const f32x4*>(&S.gm[32 * ks + 16 + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        zg[ks][r] = static_cast<bf>(static_cast<float>(zf[ks][r]) * g0[r]);
+        zg[ks][4 + r] = static_cast<bf>(static_cast<float>(zf[ks][4 + r]) * g1[r]);
+      }
+    }
+    if (w < 2) zf[1] = zg[1] = frag{};  // above the diagonal (not formed)
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt) {
+      f32x4 acc = M::mma(frag_down_rows_swz<DK>(k_s, 0, 16 * mt, lane), zg[0], zero4());
+      acc = M::mma(frag_down_rows_swz<DK>(k_s, 32, 16 * mt, lane), zg[1], acc);
+      wreg[mt] = pack(acc);
+      *reinterpret_cast<bf16x4*>(S.w + swz<DK>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1)) = wreg[mt];
+    }
+#pragma unroll
+    for (int mt = 0; mt < VT; ++mt) {
+      ureg[mt] = M::mma(frag_down_rows_swz<DV>(S.v, 0, 16 * mt, lane), zf[0], zero4());
+      ureg[mt] = M::mma(frag_down_rows_swz<DV>(S.v, 32, 16 * mt, lane), zf[1], ureg[mt]);
+    }
+  }
+  // ---- A_c^T = T_G^T P_G^T, masked by the levels of the chunk; intra-chunk output rows t
+  f32x4 oacc[VT];
+  {
+    bf16x4 a4[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      f32x4 acc = zero4();
+#pragma unroll
+      for (int ks = st / 2; ks < 2; ++ks) acc = M::mma(frag_down_rows_swz<C>(z_s, 32 * ks, 16 * st, lane), pg[ks], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = 16 * st + 4 * g + r;
+        float x = acc[r];
+        if constexpr (HAS_LAMBDA) x *= lam_h[t_own * NL + level_local(t_own, s)];
+        acc[r] = s <= t_own ? x : 0.f;
+      }
+      a4[st] = pack(acc);
+    }
+    const frag a0 = join(a4[0], a4[1]), a1 = join(a4[2], a4[3]);
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) {
+      oacc[vt] = M::mma(a0, frag_down_rows_swz<DV>(S.v, 0, 16 * vt, lane), zero4());
+      oacc[vt] = M::mma(a1, frag_down_rows_swz<DV>(S.v, 32, 16 * vt, lane), oacc[vt]);
+    }
+  }
+  __syncthreads();  // W of both chunks
+
+  // ---- Qc^T = gamma Q^T - W^T P_G^T (columns t); U over the wave's own rows of Q
+  f32x4 qc[KT];
+  {
+    const float gt = S.gm[t_own];
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt) {
+      const bf16x4 qv = *reinterpret_cast<const bf16x4*>(S.q + swz<DK>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1));
+      f32x4 acc = M::mma(frag_down_rows_swz<DK>(S.w, 0, 16 * mt, lane), pg[0], zero4());
+      acc = M::mma(frag_down_rows_swz<DK>(S.w, 32, 16 * mt, lane), pg[1], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) qc[mt][r] = gt * static_cast<float>(qv[r]) - acc[r];
+    }
+  }
+  // Qc pieces: tiles mt, mt + 1 at once (pair_rows)
+  bf* qc_row = qc_out + cidx * (C * DK) + t_own * DK + 16 * (g & 1) + 8 * (g >> 1);
+  float* oin = oin_out + cidx * (C * DV) + w * (VT * 256) + 4 * lane;
+  // U of chunk 1 in fp32, handed to the wave of chunk 0 that continues it, over V (no longer read)
+  float* u1 = reinterpret_cast<float*>(w < 2 ? S1.v : S0.v) + (w & 1) * (VT * 256) + 4 * lane;
+  if (hf == 0) {
+#pragma unroll
+    for (int mt = 0; mt < VT; ++mt)
+      *reinterpret_cast<bf16x4*>(S.q + swz<DV>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1)) = pack(ureg[mt]);
+#pragma unroll
+    for (int mt = 0; mt < KT; mt += 2)
+      *reinterpret_cast<bf16x8*>(qc_row + 16 * mt) = pair_rows(pack(qc[mt]), pack(qc[mt + 1]));
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) *reinterpret_cast<f32x4*>(oin + 256 * vt) = oacc[vt];
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < VT; ++mt) *reinterpret_cast<f32x4*>(u1 + 256 * mt) = ureg[mt];
+  }
+  __syncthreads();  // U of both chunks
+
+  // ---- chunk 1 through chunk 0: half 1 its queries and output, half 0 its W and U (wave w: row tile w)
+  const float g0 = S0.gm[C - 1];
+  // x (rows of chunk 1, operand fragments over d) times K~_0^T, transposed (k = s of chunk 0)
+  auto through = [&](const frag (&x)[KS], f32x4 (&out)[4]) {
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      f32x4 acc = zero4();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) acc = M::mma(frag_along_row_perm<DK>(S0.k, 16 * st, 32 * ks, lane), x[ks], acc);
+      out[st] = acc * *reinterpret_cast<const f32x4*>(&S0.dc[16 * st + 4 * g]);
+    }
+  };
+  if (hf == 1) {
+    const float l7 = HAS_LAMBDA ? lam_h[t_own * NL + NL - 1] : 1.f;
+    frag gq[2], gl[2];  // the second times lambda
+    {
+      frag qf[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) qf[ks] = join(pack(qc[2 * ks]), pack(qc[2 * ks + 1]));
+      f32x4 aq[4];
+      through(qf, aq);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        gq[ks] = join(pack(aq[2 * ks]), pack(aq[2 * ks + 1]));
+        gl[ks] = join(pack(aq[2 * ks] * l7), pack(aq[2 * ks + 1] * l7));
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt) {
+      f32x4 x = M::mma(frag_down_rows_swz<DK>(S0.w, 0, 16 * mt, lane), gq[0], zero4());
+      x = M::mma(frag_down_rows_swz<DK>(S0.w, 32, 16 * mt, lane), gq[1], x);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) qc[mt][r] = g0 * qc[mt][r] - x[r];
+    }
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) {
+      oacc[vt] = M::mma(gl[0], frag_down_rows_swz<DV>(S0.q, 0, 16 * vt, lane), oacc[vt]);
+      oacc[vt] = M::mma(gl[1], frag_down_rows_swz<DV>(S0.q, 32, 16 * vt, lane), oacc[vt]);
+    }
+    if (valid) {
+#pragma unroll
+      for (int mt = 0; mt < KT; mt += 2)
+        *reinterpret_cast<bf16x8*>(qc_row + 16 * mt) = pair_rows(pack(qc[mt]), pack(qc[mt + 1]));
+#pragma unroll
+      for (int vt = 0; vt < VT; ++vt) *reinterpret_cast<f32x4*>(oin + 256 * vt) = oacc[vt];
+    }
+  } else {
+    auto w_at = [&](int mt) { return reinterpret_cast<bf16x4*>(S1.w + swz<DK>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1)); };
+    frag wf[KS], gw[2];
+    f32x4 aw[4];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) wf[ks] = join(*w_at(2 * ks), *w_at(2 * ks + 1));
+    through(wf, aw);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) gw[ks] = join(pack(aw[2 * ks]), pack(aw[2 * ks + 1]));
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt) {
+      f32x4 x = M::mma(frag_down_rows_swz<DK>(S0.w, 0, 16 * mt, lane), gw[0], zero4());
+      x = M::mma(frag_down_rows_swz<DK>(S0.w, 32, 16 * mt, lane), gw[1], x);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = g0 * static_cast<float>(wf[mt / 2][4 * (mt & 1) + r]) - x[r];
+      *w_at(mt) = pack(x);
+    }
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) {
+      f32x4 x = M::mma(frag_down_rows_swz<DV>(S0.q, 0, 16 * vt, lane), gw[0], zero4());
+      x = M::mma(frag_down_rows_swz<DV>(S0.q, 32, 16 * vt, lane), gw[1], x);
+      const f32x4 u = *reinterpret_cast<const f32x4*>(u1 + 256 * vt);
+      *reinterpret_cast<bf16x4*>(S1.q + swz<DV>(t_own, 2 * vt + (g >> 1)) + 4 * (g & 1)) = pack(u - x);
+    }
+  }
+  __syncthreads();  // W_1', U_1'
+
+  // ---- P = gamma_0 gamma_1 I - K~^T W (half 0) and H = K~^T U (half 1) over the pair's 128 tokens: RT row
+  //      tiles of d_k per wave, their K~ fragments scaled once, each operand of W or U read for all of them
+  constexpr int RT = KT / 4;
+  const float gt1 = S1.gm[C - 1], gp = g0 * gt1;
+  frag ka[RT][4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const PairHalf<DK, DV>& X = half_s[ks >> 1];
+    const int r0 = 32 * (ks & 1);
+    const float sc = ks < 2 ? gt1 : 1.f;
+    const f32x4 d0 = *reinterpret_cast<const f32x4*>(&X.dc[r0 + 4 * g]) * sc;
+    const f32x4 d1 = *reinterpret_cast<const f32x4*>(&X.dc[r0 + 16 + 4 * g]) * sc;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      ka[i][ks] = frag_down_rows_swz<DK>(X.k, r0, 16 * (RT * w + i), lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        ka[i][ks][r] = static_cast<bf>(static_cast<float>(ka[i][ks][r]) * d0[r]);
+        ka[i][ks][4 + r] = static_cast<bf>(static_cast<float>(ka[i][ks][4 + r]) * d1[r]);
+      }
+    }
+  }
+  if (it + gridDim.x < npairs) {
+    cur = where(it + gridDim.x);
+    load_inputs(cur, tid);
+  } else {  // no value of this turn is kept to the next (the registers are free in between)
+    la_r = bt_r = 0.f;
+#pragma unroll
+    for (int e = 0; e < NLW; ++e) lam_r[e] = 0.f;
+#pragma unroll
+    for (int e = 0; e < PCS; ++e) kpre[e] = qpre[e] = vpre[e] = bf16x8{};
+  }
+  // product tiles (column tiles nt, nt + 1 of W or U), in the kfrag layout (eight rows of a column per
+  // lane) or row-major from the transposed product (eight columns of a row)
+  auto products = [&](auto is_p, auto transposed, bf* out) {
+    constexpr bool P = decltype(is_p)::value, TR = decltype(transposed)::value;
+#pragma unroll 1
+    for (int nt = 0; nt < KT; nt += 2) {
+      f32x4 acc[2][RT];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < RT; ++i) acc[c][i] = zero4();
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const frag x = frag_down_rows_swz<DK>(P ? half_s[ks >> 1].w : half_s[ks >> 1].q, 32 * (ks & 1), 16 * (nt + c), lane);
+#pragma unroll
+          for (int i = 0; i < RT; ++i) acc[c][i] = TR ? M::mma(x, ka[i][ks], acc[c][i]) : M::mma(ka[i][ks], x, acc[c][i]);
+        }
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        const int rt = RT * w + i;
+        if constexpr (P) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const int d = 16 * rt + (TR ? r16 : 4 * g), e = 16 * (nt + c) + (TR ? 4 * g : r16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[c][i][r] = ((TR ? d == e + r : d + r == e) ? gp : 0.f) - acc[c][i][r];
+          }
+        }
+        const int n8 = 8 * (g >> 1), n = nt + (g & 1);  // the lane's piece: rows (or columns) n8 .. + 7 of tile n
+        *reinterpret_cast<bf16x8*>(out + (TR ? (16 * rt + r16) * DK + 16 * n + n8 : kfrag_idx<DK>(16 * rt + n8, 16 * n + r16))) =
+            pair_rows(pack(acc[0][i]), pack(acc[1][i]));
+      }
+    }
+  };
+  bf* pz = pz_out + (bh * N2 + zp) * (DK * DK);
+  bf* hz = hz_out + (bh * N2 + zp) * (DK * DV);
+  if (hf == 1) products(std::false_type{}, std::false_type{}, hz);
+  else if (zp & 1) products(std::true_type{}, std::true_type{}, pz);
+  else products(std::true_type{}, std::false_type{}, pz);
+  }  // pair loop
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -610,19 +708,20 @@ __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ l
   const int64_t tok0 = (int64_t)b * Tlen + z * C;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int J = N <= 1 ? 0 : 32 - __builtin_clz((unsigned)(N - 1));
+  const int64_t zp = z >> 1, N2 = (N + 1) >> 1;  // the chunk's pair; pairs of the sequence
+  const int J = N2 <= 1 ? 0 : 32 - __builtin_clz((unsigned)(N2 - 1));
 
   // node fragments of the level at bit m: A(G) for this wave's output columns, and T(G) for its
   // q~ columns when a higher level follows.  The first level's are loaded before Q~ is staged.
   frag ba[VT][KS], bt[KT][KS];
   auto load_level = [&](int m, bool with_t) {
-    const int64_t kblk = (z >> m) - 1;
+    const int64_t kblk = (zp >> m) - 1;
     const bf *tn, *an;
     if (m == 0) {
-      tn = pz + (bh * N + kblk) * (DK * DK);
-      an = hz + (bh * N + kblk) * (DK * DV);
+      tn = pz + (bh * N2 + kblk) * (DK * DK);
+      an = hz + (bh * N2 + kblk) * (DK * DV);
     } else {
-      tn = tree + tree_level_offset(BH, N, m, BS) + (bh * (N >> m) + kblk) * BS;
+      tn = tree + tree_level_offset(BH, N2, m, BS) + (bh * (N2 >> m) + kblk) * BS;
       an = tn + DK * DK;
     }
 #pragma unroll
@@ -636,7 +735,7 @@ __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ l
         for (int ks = 0; ks < KS; ++ks) bt[v][ks] = MF::load(tn + (((KT * wave + v) * KS + ks) * 64 + lane) * 8);
     }
   };
-  unsigned bits = (unsigned)z;
+  unsigned bits = (unsigned)zp;
   if (bits) load_level(__builtin_ctz(bits), (bits & (bits - 1)) != 0);
 
   for (int x = tid; x < C * DK / 8; x += 256) {
@@ -647,7 +746,7 @@ __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ l
   if constexpr (HAS_LAMBDA) {
     for (int x = tid; x < C * J; x += 256) {
       const int t = x / J, jj = x % J;
-      lw_s[t * kMaxJ + jj] = lam[((tok0 + t) * H + h) * L + LOG2C + 1 + jj];
+      lw_s[t * kMaxJ + jj] = lam[((tok0 + t) * H + h) * L + LOG2C + 2 + jj];
     }
   }
   __syncthreads();
@@ -660,7 +759,7 @@ __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ l
   int cur = 0;
   bool first = true;
   while (bits) {
-    const int m = __builtin_ctz(bits);  // tree level of the source group; token level log2 C + m + 1
+    const int m = __builtin_ctz(bits);  // tree level of the source group; token level log2 C + m + 2
     bits &= bits - 1;
     if (!first) load_level(m, bits != 0);
     first = false;
@@ -747,16 +846,16 @@ __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ l
 // Host side
 // ---------------------------------------------------------------------------------------------
 int64_t gdn_workspace(int64_t B, int64_t T, int64_t H, int64_t dk, int64_t dv, int64_t C, GdnLayout* lay) {
-  const int64_t N = T / C, BHN = B * H * N;
+  const int64_t N = T / C, BHN = B * H * N, N2 = (N + 1) / 2, BHP = B * H * N2;
   auto al = [](int64_t x) { return (x + 255) & ~int64_t(255); };
   GdnLayout w{};
   int64_t cur = 0;
   w.qc = cur; cur += al(BHN * C * dk * 2);
-  w.pz = cur; cur += al(BHN * dk * dk * 2);
-  w.hz = cur; cur += al(BHN * dk * dv * 2);
+  w.pz = cur; cur += al(BHP * dk * dk * 2);
+  w.hz = cur; cur += al(BHP * dk * dv * 2);
   w.oin = cur; cur += al(BHN * C * dv * 4);
-  int64_t blocks = 0;  // tree levels 1 .. J-1 (the source groups of 2 .. 2^(J-1) chunks)
-  for (int64_t m = 1; (int64_t(1) << m) < N; ++m) blocks += N >> m;
+  int64_t blocks = 0;  // tree levels 1 .. J-1 (the source groups of 2 .. 2^(J-1) pairs of chunks)
+  for (int64_t m = 1; (int64_t(1) << m) < N2; ++m) blocks += N2 >> m;
   w.tree = cur; cur += al(B * H * blocks * dk * (dk + dv) * 2);
   w.total = cur;
   if (lay) *lay = w;
@@ -775,37 +874,38 @@ hipError_t launch_gdn(const GdnArgs& a, hipStream_t st, hipEvent_t* ev) {
   __bf16* pz = reinterpret_cast<__bf16*>(base + w.pz);
   __bf16* hz = reinterpret_cast<__bf16*>(base + w.hz);
   float* oin = reinterpret_cast<float*>(base + w.oin);
-  const int64_t N = a.T / C;
-  const int J = N <= 1 ? 0 : 64 - __builtin_clzll(uint64_t(N - 1));
-  // the chunk kernel runs one persistent workgroup per compute unit (its LDS allows no more)
+  const int64_t N = a.T / C, N2 = (N + 1) / 2;
+  const int J = N2 <= 1 ? 0 : 64 - __builtin_clzll(uint64_t(N2 - 1));
   const int64_t nchunks = a.B * a.H * N;
+  // the pair kernel runs one persistent workgroup per compute unit
+  const int64_t npairs = a.B * a.H * N2;
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
     ncu = 256;
-  const dim3 g1((unsigned)(nchunks < ncu ? nchunks : ncu));
+  const dim3 g1((unsigned)(npairs < ncu ? npairs : ncu));
   const __bf16* q = static_cast<const __bf16*>(a.q);
   const __bf16* k = static_cast<const __bf16*>(a.k);
   const __bf16* v = static_cast<const __bf16*>(a.v);
   __bf16* o = static_cast<__bf16*>(a.o);
   if (ev) (void)hipEventRecord(ev[0], st);
   if (a.lambda)
-    hipLaunchKernelGGL((gdn::k_gdn_chunk<C, DK, DV, true>), g1, dim3(64 * gdn::kChunkWaves), 0, st, q, k, v, a.log_alpha, a.beta,
-                       a.lambda, qc, pz, hz, oin, a.T, (int)a.H, a.L, nchunks);
+    hipLaunchKernelGGL((gdn::k_gdn_pair<DK, DV, true>), g1, dim3(512), 0, st, q, k, v, a.log_alpha, a.beta, a.lambda, qc,
+                       pz, hz, oin, a.T, (int)a.H, a.L, npairs);
   else
-    hipLaunchKernelGGL((gdn::k_gdn_chunk<C, DK, DV, false>), g1, dim3(64 * gdn::kChunkWaves), 0, st, q, k, v, a.log_alpha, a.beta,
-                       a.lambda, qc, pz, hz, oin, a.T, (int)a.H, a.L, nchunks);
+    hipLaunchKernelGGL((gdn::k_gdn_pair<DK, DV, false>), g1, dim3(512), 0, st, q, k, v, a.log_alpha, a.beta, a.lambda,
+                       qc, pz, hz, oin, a.T, (int)a.H, a.L, npairs);
   if (ev) (void)hipEventRecord(ev[1], st);
   // the block tree, one level per launch (level m from level m - 1; level 0 = P_z, H_z)
   __bf16* tree = reinterpret_cast<__bf16*>(base + w.tree);
   const int64_t BH = a.B * a.H, BS = (int64_t)DK * (DK + DV);
   for (int m = 1; m < J; ++m) {
-    const __bf16* tin = m == 1 ? pz : tree + gdn::tree_level_offset(BH, N, m - 1, BS);
+    const __bf16* tin = m == 1 ? pz : tree + gdn::tree_level_offset(BH, N2, m - 1, BS);
     const __bf16* ain = m == 1 ? hz : tin + DK * DK;
     const int64_t ts = m == 1 ? DK * DK : BS, as = m == 1 ? DK * DV : BS;
-    const int64_t nin = m == 1 ? N : (N >> (m - 1));
+    const int64_t nin = m == 1 ? N2 : (N2 >> (m - 1));
     constexpr int split = (DK + DV) / 16 / gdn::kCombineTiles;
-    hipLaunchKernelGGL((gdn::k_gdn_combine<DK, DV>), dim3((unsigned)((N >> m) * split), (unsigned)BH), dim3(256), 0, st,
-                       tin, ain, ts, as, nin, tree + gdn::tree_level_offset(BH, N, m, BS), N >> m);
+    hipLaunchKernelGGL((gdn::k_gdn_combine<DK, DV>), dim3((unsigned)((N2 >> m) * split), (unsigned)BH), dim3(256), 0, st,
+                       tin, ain, ts, as, nin, tree + gdn::tree_level_offset(BH, N2, m, BS), N2 >> m);
   }
   const dim3 g2((unsigned)nchunks);
   if (a.lambda)
