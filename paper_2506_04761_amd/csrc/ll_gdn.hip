@@ -208,7 +208,8 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
   }
   __syncthreads();
 
-  // ---- L[t][s] = beta_t (k_t . k_s) Gamma[t,s], s < t: the wave's diagonal block and some of the others
+  // ---- L[t][s] = beta_t (k_t . k_s) Gamma[t,s], s < t, in 16 x 16 blocks (result layout): the wave's diagonal
+  //      block stays in registers, the others (some per wave) go to LDS
   auto form_l = [&](int i, int j) {
     f32x4 acc = zero4();
 #pragma unroll
@@ -221,32 +222,33 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float y = bt[r] * acc[r] * fast_exp2(fminf(ct[r] - cs, 0.f));
-      l_s[blk(i, j) + blk_at(4 * g + r, r16)] = s < 16 * i + 4 * g + r ? y : 0.f;
+      acc[r] = s < 16 * i + 4 * g + r ? y : 0.f;
     }
+    return acc;
   };
-  form_l(w, w);
-  if (w == 0) { form_l(1, 0); form_l(2, 0); }
-  if (w == 1) { form_l(2, 1); form_l(3, 0); }
-  if (w == 2) form_l(3, 1);
-  if (w == 3) form_l(3, 2);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  auto put_l = [&](int i, int j) {
+    const f32x4 y = form_l(i, j);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) l_s[blk(i, j) + blk_at(4 * g + r, r16)] = y[r];
+  };
+  const f32x4 ld = form_l(w, w);
+  if (w == 0) { put_l(1, 0); put_l(2, 0); }
+  if (w == 1) { put_l(2, 1); put_l(3, 0); }
+  if (w == 2) put_l(3, 1);
+  if (w == 3) put_l(3, 2);
   // ---- X = (I + L)^-1 in 16 x 16 blocks (fp32), T_G = X diag(beta).  Each wave inverts its diagonal block by
-  //      forward substitution (lane c of every 16: column c), then the blocks (1,0) and (3,2), then the
-  //      32 x 32 block below: X_21 = -X_22 (L_21 X_11) in halves of 32 rows.
+  //      forward substitution (lane c of every 16: column c; L_ij from its lane, no LDS: all waves' broadcast
+  //      reads of it took 2500 clocks), then the blocks (1,0) and (3,2), then the 32 x 32 block below,
+  //      X_21 = -X_22 (L_21 X_11), whose products with diagonal blocks are formed before the barrier.
   auto put_z = [&](int t, int c, float x) { z_s[swz<C>(t, c >> 3) + (c & 7)] = static_cast<bf>(x * S.bt[c]); };
   {
-    const float* lb = l_s + blk(w, w);
     float x[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       f32x4 a = zero4();
 #pragma unroll
-      for (int j = 0; j < i; j += 4) {
-        const f32x4 lv = *reinterpret_cast<const f32x4*>(&lb[blk_at(i, j)]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (j + e < i) a[e] += lv[e] * x[j + e];
-      }
+      for (int j = 0; j < i; ++j)
+        a[j & 3] += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ld[i & 3]), 16 * (i >> 2) + j)) * x[j];
       const float acc = ((i == r16) ? 1.f : 0.f) - ((a[0] + a[1]) + (a[2] + a[3]));
       x[i] = (i < r16) ? 0.f : acc;
     }
@@ -275,6 +277,8 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
     for (int r = 0; r < 4; ++r) acc = MF::mma(x_s[blk(i, kb) + blk_at(r16, 4 * g + r)], y[r], acc);
     return acc;
   };
+  const int bi = 2 + (w >> 1), bj = w & 1;  // the wave's block of X_21
+  f32x4 y2 = lx_mul(2, bj, bj, zero4()), y3 = lx_mul(3, bj, bj, zero4());  // L_2j X_jj, L_3j X_jj
   if (!(w & 1)) {
     const f32x4 x = xy_mul(w + 1, w + 1, lx_mul(w + 1, w, w, zero4()), zero4());
 #pragma unroll
@@ -285,17 +289,14 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
   }
   __syncthreads();
   {
-    const int i = 2 + (w >> 1), j = w & 1;
-    f32x4 y2 = lx_mul(2, 1, j, zero4());
-    if (j == 0) y2 = lx_mul(2, 0, 0, y2);
-    f32x4 x = xy_mul(i, 2, y2, zero4());
-    if (i == 3) {
-      f32x4 y3 = lx_mul(3, 1, j, zero4());
-      if (j == 0) y3 = lx_mul(3, 0, 0, y3);
-      x = xy_mul(3, 3, y3, x);
+    if (bj == 0) {
+      y2 = lx_mul(2, 1, 0, y2);
+      y3 = lx_mul(3, 1, 0, y3);
     }
+    f32x4 x = xy_mul(bi, 2, y2, zero4());
+    if (bi == 3) x += xy_mul(3, 3, y3, zero4());
 #pragma unroll
-    for (int r = 0; r < 4; ++r) put_z(16 * i + 4 * g + r, 16 * j + r16, -x[r]);
+    for (int r = 0; r < 4; ++r) put_z(16 * bi + 4 * g + r, 16 * bj + r16, -x[r]);
   }
   __syncthreads();  // T_G complete; L and X free for W
 
