@@ -131,14 +131,13 @@ __device__ inline int swz(int r, int c) {
 // waves in turn.  Rows at or beyond `nrow` are filled from row nrow - 1 (callers never read
 // them).  The copy is complete once the issuing wave has waited for its vector-memory operations.
 // AUX: cache-policy bits of the loads (0 by default; 2, non-temporal, for data read once).
-// The NT threads are waves 0 .. NT/64 - 1 of the workgroup, or `wave` is the wave's index among them.
 template <int D, int ROWS, int NT, int AUX = 0>
-__device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src, int64_t stride, int nrow,
-                                     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+__device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src, int64_t stride, int nrow) {
   constexpr int CH = D / 8;      // chunks per row
   constexpr int RPI = NT / CH;   // rows per pass of all waves
   static_assert(NT % CH == 0 && RPI % CH == 0 && ROWS % RPI == 0, "whole rows per pass");
   const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q0 = wave * 64 + lane;                     // chunk position in the first pass
   const int r0 = q0 / CH, c = (q0 % CH) ^ (r0 & (CH - 1));  // the swizzle repeats every pass
 #pragma unroll

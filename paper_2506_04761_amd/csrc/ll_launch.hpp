@@ -75,10 +75,6 @@ const KernelEntry* mamba2_table(int* n);
 // The tag of the summaries formed from `a` (storage element size esize); magic = 0 gives a tag that
 // matches nothing.
 WsTag mamba2_tag(const Mamba2Args& a, int64_t esize, bool valid);
-// Enqueues the write of `tag` into the workspace's tag region.
-hipError_t launch_write_tag(void* workspace, const WsLayout& w, const WsTag& tag, hipStream_t st);
-// Enqueues the write of `tag` at `dst` (a workspace's tag region).
-hipError_t launch_write_tag_at(void* dst, const WsTag& tag, hipStream_t st);
 
 // Single-pass forward (ll_mamba2_fused.hip): byte offsets of its workspace regions.
 struct FusedLayout {
@@ -105,7 +101,6 @@ hipError_t launch_mamba2_fused(const Mamba2Args& a, hipStream_t st, hipEvent_t* 
 // summaries (byte offsets).
 struct BwdLayout {
   WsLayout fwd;
-  int64_t bad = 0;  // 256 bytes: set when the forward summaries to be reused belong to other inputs
   int64_t NR = 0, nd = 0, npart = 0;  // 8-tile regions; key-side summaries and partials per (b, h)
   int64_t d = 0, dtot = 0, part = 0, qdq = 0, tsum = 0, dqh = 0, dkh = 0, total = 0;
 };

@@ -46,7 +46,10 @@ template <typename T, int C, int DK, int DV, bool HAS_LAMBDA>
 __global__ __launch_bounds__(kStateThreads) void k_block_state(const T* __restrict__ k, const T* __restrict__ v,
                                                      const float* __restrict__ log_alpha, Nodes<T> nodes,
                                                      T* __restrict__ tiles, float* __restrict__ tot2_out,
-                                                     int64_t Tlen, int H, int Hqk) {
+                                                     int64_t Tlen, int H, int Hqk,
+    uint64_t* __restrict__ tag_dst, WsTag tag) {
+  // the workspace's tag (read by later launches only)
+  if (blockIdx.x == 0 && threadIdx.x < 12) tag_dst[threadIdx.x] = tag.v[threadIdx.x];
   using M = Mfma<T>;
   typedef typename Vec16<T>::type V16;
   constexpr int R = tile_rows(C);
@@ -1105,10 +1108,6 @@ int64_t mamba2_workspace(int64_t B, int64_t T, int64_t H, int64_t dk, int64_t dv
   return cur;
 }
 
-__global__ void k_write_tag(uint64_t* dst, WsTag tag) {
-  if (threadIdx.x < 12) dst[threadIdx.x] = tag.v[threadIdx.x];
-}
-
 WsTag mamba2_tag(const Mamba2Args& a, int64_t esize, bool valid) {
   WsTag t{};
   t.v[0] = valid ? kWsTagMagic : 0;
@@ -1126,23 +1125,19 @@ WsTag mamba2_tag(const Mamba2Args& a, int64_t esize, bool valid) {
   return t;
 }
 
-hipError_t launch_write_tag_at(void* dst, const WsTag& tag, hipStream_t st) {
-  hipLaunchKernelGGL(k_write_tag, dim3(1), dim3(64), 0, st, static_cast<uint64_t*>(dst), tag);
-  return hipGetLastError();
+static uint64_t* tag_region(void* workspace, const WsLayout& w) {
+  return reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + w.tag);
 }
 
-hipError_t launch_write_tag(void* workspace, const WsLayout& w, const WsTag& tag, hipStream_t st) {
-  return launch_write_tag_at(static_cast<char*>(workspace) + w.tag, tag, st);
-}
-
-// Also records, once the summaries are complete, the tag of the inputs they were formed from.
+// Also records the tag of the inputs the summaries are formed from.
 template <typename T, int C, int DK, int DV>
 hipError_t launch_mamba2_summaries(const Mamba2Args& a, const WsLayout& w, const Nodes<T>& nodes, hipStream_t st,
                                    hipEvent_t ev_mid) {
   constexpr int SZ = DK * DV;
   const dim3 gblk((unsigned)(w.nb * a.H * a.B));
   hipLaunchKernelGGL((k_block_state<T, C, DK, DV, true>), gblk, dim3(kStateThreads), 0, st, (const T*)a.k, (const T*)a.v,
-                     a.log_alpha, nodes, (T*)nullptr, const_cast<float*>(nodes.t1), a.T, (int)a.H, (int)a.Hqk);
+                     a.log_alpha, nodes, (T*)nullptr, const_cast<float*>(nodes.t1), a.T, (int)a.H, (int)a.Hqk,
+                     tag_region(a.workspace, w), mamba2_tag(a, sizeof(T), true));
   if (ev_mid) (void)hipEventRecord(ev_mid, st);
   if (w.J >= 4) {
     // LDS: the totals tree (the block count rounded up to whole chunks, and its levels)
@@ -1158,7 +1153,7 @@ hipError_t launch_mamba2_summaries(const Mamba2Args& a, const WsLayout& w, const
       hipLaunchKernelGGL((k_level_scan<T, kMaxLevels>), glev, dim3(kScanThreads), tt * sizeof(float), st, nodes, w.N,
                          w.J, SZ);
   }
-  return launch_write_tag(a.workspace, w, mamba2_tag(a, sizeof(T), true), st);
+  return hipGetLastError();
 }
 
 // Enqueues the stages on `st`.  With `ev` non-null, ev[i] is recorded before stage i and ev[3]
@@ -1184,13 +1179,11 @@ hipError_t launch_mamba2(const Mamba2Args& a, hipStream_t st, hipEvent_t* ev) {
     const hipError_t e = launch_mamba2_summaries<T, C, DK, DV>(a, w, nodes, st, ev ? ev[1] : nullptr);
     if (e != hipSuccess) return e;
   } else {
-    // the workspace no longer holds level summaries
-    const hipError_t e = launch_write_tag(a.workspace, w, mamba2_tag(a, sizeof(T), false), st);
-    if (e != hipSuccess) return e;
     const dim3 gblk((unsigned)(w.nb * a.H * a.B));
     const dim3 gscan((unsigned)((SZ / 2 + 255) / 256), (unsigned)(a.B * a.H));
     hipLaunchKernelGGL((k_block_state<T, C, DK, DV, false>), gblk, dim3(kStateThreads), 0, st, (const T*)a.k, (const T*)a.v,
-                       a.log_alpha, nodes, tiles, const_cast<float*>(nodes.t1), a.T, (int)a.H, (int)a.Hqk);
+                       a.log_alpha, nodes, tiles, const_cast<float*>(nodes.t1), a.T, (int)a.H, (int)a.Hqk,
+                       tag_region(a.workspace, w), mamba2_tag(a, sizeof(T), false));  // no level summaries
     if (ev) (void)hipEventRecord(ev[1], st);
     hipLaunchKernelGGL((k_running_scan<T>), gscan, dim3(256), w.N * sizeof(float), st, (const T*)tiles, running,
                        (const float*)nodes.t1, w.N, SZ);

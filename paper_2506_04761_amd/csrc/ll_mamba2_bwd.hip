@@ -1340,11 +1340,17 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_bwd_dgate: grid (ceil(T / 256), B * H); adds to each row's tile-local suffix sum the totals
-// of all later tiles of its sequence.
+// k_bwd_dgate: grid (ceil(T / 256), B * H), the last launch; adds to each row's tile-local suffix sum the
+// totals of all later tiles of its sequence.  With `tag` non-null (reused summaries) it compares the
+// workspace's tag with that of this call's inputs and, where they differ, fills the rows' gradients
+// with NaN instead (every head its own, the first head of a group the shared dq and dk): launches of
+// their own for the comparison and the filling took 6 us of a 190 us step (T = 4032, 12 heads).
 // ---------------------------------------------------------------------------------------------
+template <typename T, int DK, int DV>
 __global__ __launch_bounds__(256) void k_bwd_dgate(const float* __restrict__ tsum, float* __restrict__ dla,
-                                                   int64_t Tlen, int H, int R) {
+                                                   int64_t Tlen, int H, int R, const uint64_t* __restrict__ tag,
+                                                   WsTag want, T* __restrict__ dq, T* __restrict__ dk,
+                                                   T* __restrict__ dv, float* __restrict__ dlam, int Hqk, int L) {
   __shared__ float red_s[4];
   const int64_t N = (Tlen + R - 1) / R;
   const int64_t bh = blockIdx.y;
@@ -1353,6 +1359,22 @@ __global__ __launch_bounds__(256) void k_bwd_dgate(const float* __restrict__ tsu
   const int64_t t1 = t0 + 255 < Tlen - 1 ? t0 + 255 : Tlen - 1;
   const int64_t ulast = t1 / R;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tag && __any(lane < 12 && tag[lane < 12 ? lane : 0] != want.v[lane < 12 ? lane : 0])) {
+    const float fn = __builtin_nanf("");
+    const T tn = from_f32<T>(fn);
+    const int rows = (int)(t1 - t0 + 1), G = H / Hqk;
+    const int64_t row0 = (int64_t)b * Tlen + t0;
+    for (int i = tid; i < rows * DV; i += 256) dv[((row0 + i / DV) * H + h) * DV + i % DV] = tn;
+    for (int i = tid; i < rows * L; i += 256) dlam[((row0 + i / L) * H + h) * L + i % L] = fn;
+    for (int i = tid; i < rows; i += 256) dla[(row0 + i) * H + h] = fn;
+    if (h % G == 0)
+      for (int i = tid; i < rows * DK; i += 256) {
+        const int64_t at = ((row0 + i / DK) * Hqk + h / G) * DK + i % DK;
+        dq[at] = tn;
+        dk[at] = tn;
+      }
+    return;
+  }
   float s = 0.f;
   for (int64_t x = ulast + 1 + tid; x < N; x += 256) s += tsum[bh * N + x];
 #pragma unroll
@@ -1410,7 +1432,6 @@ int64_t mamba2_bwd_workspace(int64_t B, int64_t T, int64_t H, int64_t Hqk, int64
   w.npart = 0;
   for (int j = 5; j <= J; ++j) w.npart += RevNodes<float>::parts(w.NR, j);
   const int64_t nd1 = w.nd > 0 ? w.nd : 1, np1 = w.npart > 0 ? w.npart : 1;
-  w.bad = cur; cur += al(4);
   w.d = cur; cur += al(BH * nd1 * SZ * esize);
   w.dtot = cur; cur += al(BH * nd1 * 4);
   w.part = cur; cur += al(BH * np1 * SZ * 4);
@@ -1423,28 +1444,6 @@ int64_t mamba2_bwd_workspace(int64_t B, int64_t T, int64_t H, int64_t Hqk, int64
   w.total = cur;
   if (lay) *lay = w;
   return cur;
-}
-
-// Compares the workspace's summary tag with the tag of this call's inputs: *bad = 1 on a mismatch.
-__global__ void k_check_tag(const uint64_t* tag, WsTag want, int* bad) {
-  const int i = threadIdx.x;
-  const bool diff = i < 12 && tag[i] != want.v[i];
-  const bool any = __any(diff);
-  if (i == 0) *bad = any ? 1 : 0;
-}
-
-// NaN-fills every gradient when *bad is set (the reused summaries belonged to other inputs).
-template <typename T>
-__global__ void k_poison_grads(const int* bad, T* dq, int64_t nq, T* dk, T* dv, int64_t nv, float* dla, int64_t na,
-                               float* dlam, int64_t nl) {
-  if (*bad == 0) return;
-  const T tn = from_f32<T>(__builtin_nanf(""));
-  const float fn = __builtin_nanf("");
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq; i += stride) dq[i] = dk[i] = tn;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) dv[i] = tn;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na; i += stride) dla[i] = fn;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += stride) dlam[i] = fn;
 }
 
 // Stages (ev[i] recorded before stage i, ev[4] after the last): 0 the forward summaries (skipped
@@ -1487,14 +1486,10 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
   fa.q = a.q; fa.k = a.k; fa.v = a.v; fa.log_alpha = a.log_alpha; fa.lambda = a.lambda; fa.o = nullptr;
   fa.B = a.B; fa.T = a.T; fa.H = a.H; fa.dk = DK; fa.dv = DV; fa.C = C; fa.Hqk = a.Hqk; fa.L = a.L;
   fa.workspace = a.workspace;
-  int* bad = reinterpret_cast<int*>(base + w.bad);
   if (ev) (void)hipEventRecord(ev[0], st);
   if (!a.reuse_summaries) {
     const hipError_t e = launch_mamba2_summaries<T, C, DK, DV>(fa, w.fwd, nodes, st, nullptr);
     if (e != hipSuccess) return e;
-  } else {
-    hipLaunchKernelGGL(k_check_tag, dim3(1), dim3(64), 0, st,
-                       reinterpret_cast<const uint64_t*>(base + w.fwd.tag), mamba2_tag(fa, sizeof(T), true), bad);
   }
   if (ev) (void)hipEventRecord(ev[1], st);
   if (J >= 1) {
@@ -1529,8 +1524,6 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
     hipLaunchKernelGGL((k_bwd_dkv<T, C, DK, DV>), gtile, dim3(4 * R), 0, st, (const T*)a.q, (const T*)a.k,
                        (const T*)a.v, (const T*)a.dout, a.log_alpha, a.lambda, rev, (const float*)qdq, dkh,
                        (T*)a.dv, a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J);
-  hipLaunchKernelGGL(k_bwd_dgate, dim3((unsigned)((a.T + 255) / 256), (unsigned)BH), dim3(256), 0, st,
-                     (const float*)tsum, a.dlog_alpha, a.T, (int)a.H, R);
   if (grouped) {
     const int64_t n = a.B * a.T * a.Hqk * DK;
     hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)dqh, (T*)a.dq,
@@ -1538,11 +1531,10 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
     hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)dkh, (T*)a.dk,
                        a.B * a.T, (int)a.H, (int)a.Hqk, DK);
   }
-  if (a.reuse_summaries) {
-    const int64_t nq = a.B * a.T * a.Hqk * DK, nv = a.B * a.T * a.H * DV, na = a.B * a.T * a.H;
-    hipLaunchKernelGGL((k_poison_grads<T>), dim3(512), dim3(256), 0, st, (const int*)bad, (T*)a.dq, nq, (T*)a.dk,
-                       (T*)a.dv, nv, a.dlog_alpha, na, a.dlambda, na * a.L);
-  }
+  const uint64_t* tag = a.reuse_summaries ? reinterpret_cast<const uint64_t*>(base + w.fwd.tag) : nullptr;
+  hipLaunchKernelGGL((k_bwd_dgate<T, DK, DV>), dim3((unsigned)((a.T + 255) / 256), (unsigned)BH), dim3(256), 0, st,
+                     (const float*)tsum, a.dlog_alpha, a.T, (int)a.H, R, tag, mamba2_tag(fa, sizeof(T), true),
+                     (T*)a.dq, (T*)a.dk, (T*)a.dv, a.dlambda, (int)a.Hqk, a.L);
   if (ev) (void)hipEventRecord(ev[4], st);
   return hipGetLastError();
 }

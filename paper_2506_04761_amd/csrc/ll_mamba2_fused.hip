@@ -63,7 +63,8 @@ struct FusedWs {
   float* bsum;     // [BH][stride] aligned block sums of tile totals; level b at sum_{b'<b} ceil(N / 2^b')
   int* flag;       // [BH][N] 1 once node(u) is published
   unsigned* ctr;   // [0..7] ticket counters of the XCD queues, [8] waits that timed out
-  uint64_t* tag;   // the workspace's summary tag (word 0 cleared: the backward finds no summaries)
+  uint64_t* tag;   // the workspace's summary tag: the inputs of the summaries this forward leaves for the
+                   // backward, or none
   __bf16* ubwd;    // with the backward's summaries: [BH][N] node slots in [d_v][d_k] order
   float* cl;       //   [BH][N][R] tile-local cumulative log2-gates
   float* t1;       //   [BH][N] tile totals
@@ -121,7 +122,7 @@ __device__ inline bf16x8 node_frag(const __bf16* img, int dvt, int ks) {
 // ---------------------------------------------------------------------------------------------
 template <int R>
 __global__ __launch_bounds__(256) void k_fused_tiles(const float* __restrict__ log_alpha, FusedWs ws, int64_t Tlen,
-                                                     int H, int64_t N) {
+                                                     int H, int64_t N, WsTag tag) {
   __shared__ float part_s[4][16];
   const int64_t u = blockIdx.x;
   const int b = blockIdx.y;
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(256) void k_fused_tiles(const float* __restrict__ l
     __syncthreads();
   }
   if (u == 0 && b == 0 && tid < 16) ws.ctr[tid] = 0;
-  if (u == 0 && b == 0 && tid == 0) ws.tag[0] = 0;  // re-tagged after the tile kernel when the backward's summaries are left
+  if (u == 0 && b == 0 && tid < 12) ws.tag[tid] = tag.v[tid];  // read by later calls only
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(256) void k_fused_tree(FusedWs ws, int64_t N, int J
 // with the query index as the MFMA column), and the d_v tiles w MT/4 .. (w + 1) MT/4 - 1 of the
 // tile's state and node.
 // ---------------------------------------------------------------------------------------------
-template <int DK, int DV, bool HAS_LAMBDA, bool BWD_OUT>
+template <int DK, int DV, bool HAS_LAMBDA, bool BWD_OUT, bool SCAN>
 __global__ __launch_bounds__(kFastThreads, 2) void k_fused_fwd(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const float* __restrict__ log_alpha, const float* __restrict__ lam, FusedWs ws, __bf16* __restrict__ o,
@@ -263,12 +264,11 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_fused_fwd(
   if constexpr (HAS_LAMBDA) lds_copy_lambda<R, NT>(lam_s, lam, row0, H, h, L, nrow);
   lds_copy_rows<DK, R, NT>(k_s, k + (row0 * Hqk + hq) * DK, (int64_t)Hqk * DK, nrow);
   lds_copy_rows<DV, R, NT>(v_s, v + (row0 * H + h) * DV, (int64_t)H * DV, nrow);
-  const bool scan = !BWD_OUT && N <= kScanTiles;
-  float lb = 0.f;  // scan: lane x holds the total of tile u - 1 - x
-  if (scan) {
+  float lb = 0.f;  // SCAN: lane x holds the total of tile u - 1 - x
+  if constexpr (SCAN) {
     if (lane < u) lb = ws.bsum[bh * ws.stride + u - 1 - lane];
-  } else if (lane < J && ((u >> lane) & 1)) {
-    lb = ws.bsum[bh * ws.stride + bsum_offset(N, lane) + (u >> lane) - 1];
+  } else {
+    if (lane < J && ((u >> lane) & 1)) lb = ws.bsum[bh * ws.stride + bsum_offset(N, lane) + (u >> lane) - 1];
   }
   auto slot_of = [&](int j) -> int64_t { return group_end(u, j) - 1; };  // node(e - 1) covers the group ending at e
   // the flags of all the tile's source groups in one poll (lane j - 1: level j); polled again after
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_fused_fwd(
   // gap_j (lane j - 1): summed totals of the tile's lower-level source groups, i.e. of the u % 2^(j-1)
   // tiles before it
   float gapv = wave_inclusive_scan(lb);
-  if (scan) {
+  if constexpr (SCAN) {
     const int m = u & ((1 << (lane < 8 ? lane : 8)) - 1);  // levels j - 1 < 6
     const float sum = __shfl(gapv, m > 0 ? m - 1 : 0, 64);
     gapv = m > 0 ? sum : 0.f;
@@ -626,32 +626,26 @@ static hipError_t launch_fused(const Mamba2Args& a, hipStream_t st, hipEvent_t* 
   const int BH = (int)(a.B * a.H);
   if (ev) (void)hipEventRecord(ev[0], st);
   hipLaunchKernelGGL((k_fused_tiles<kFastRows>), dim3((unsigned)w.N, (unsigned)a.B), dim3(256), 0, st, a.log_alpha, ws,
-                     a.T, (int)a.H, w.N);
+                     a.T, (int)a.H, w.N, mamba2_tag(a, 2, bwd_out));
   if (ev) (void)hipEventRecord(ev[1], st);
-  if (w.J > 1 && (bwd_out || w.N > kScanTiles)) {
+  const bool scan = !bwd_out && w.N <= kScanTiles;
+  if (w.J > 1 && !scan) {
     const int64_t n1 = (w.N + 1) / 2;  // the largest level formed in LDS
     hipLaunchKernelGGL(k_fused_tree, dim3((unsigned)BH), dim3(256), (size_t)n1 * 2 * sizeof(float), st, ws, w.N, w.J);
   }
   if (ev) (void)hipEventRecord(ev[2], st);
   // every XCD receives (workgroups round-robin) as many workgroups as its queue has tiles
   const int64_t grid = (int64_t)kQueues * ((BH + kQueues - 1) / kQueues) * w.N;
-  if (bwd_out)
-    hipLaunchKernelGGL((k_fused_fwd<DK, DV, true, true>), dim3((unsigned)grid), dim3(kFastThreads), 0, st,
-                       (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, a.log_alpha, a.lambda, ws,
-                       (__bf16*)a.o, a.T, (int)a.H, (int)a.Hqk, a.L, w.J, w.N, BH);
-  else if (a.lambda)
-    hipLaunchKernelGGL((k_fused_fwd<DK, DV, true, false>), dim3((unsigned)grid), dim3(kFastThreads), 0, st,
-                       (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, a.log_alpha, a.lambda, ws,
-                       (__bf16*)a.o, a.T, (int)a.H, (int)a.Hqk, a.L, w.J, w.N, BH);
-  else
-    hipLaunchKernelGGL((k_fused_fwd<DK, DV, false, false>), dim3((unsigned)grid), dim3(kFastThreads), 0, st,
-                       (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, a.log_alpha, a.lambda, ws,
-                       (__bf16*)a.o, a.T, (int)a.H, (int)a.Hqk, a.L, w.J, w.N, BH);
-  // the summaries the backward reuses are complete: tag them with the inputs they came from
-  if (bwd_out) {
-    const hipError_t e = launch_write_tag_at(ws.tag, mamba2_tag(a, 2, true), st);
-    if (e != hipSuccess) return e;
-  }
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kFastThreads), 0, st, (const __bf16*)a.q, (const __bf16*)a.k,
+                       (const __bf16*)a.v, a.log_alpha, a.lambda, ws, (__bf16*)a.o, a.T, (int)a.H, (int)a.Hqk, a.L, w.J,
+                       w.N, BH);
+  };
+  if (bwd_out) launch(k_fused_fwd<DK, DV, true, true, false>);
+  else if (a.lambda && scan) launch(k_fused_fwd<DK, DV, true, false, true>);
+  else if (a.lambda) launch(k_fused_fwd<DK, DV, true, false, false>);
+  else if (scan) launch(k_fused_fwd<DK, DV, false, false, true>);
+  else launch(k_fused_fwd<DK, DV, false, false, false>);
   if (ev) (void)hipEventRecord(ev[3], st);
   return hipGetLastError();
 }
