@@ -152,8 +152,8 @@ __device__ inline void lds_copy_rows(__bf16* dst, const __bf16* __restrict__ src
 
 // bf16 MFMA operand fragment down the rows of a swizzled tile (as frag_down_rows).
 template <int D>
-__device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0, int lane = threadIdx.x & 63) {
-  const int g = lane >> 4, i = lane & 15;
+__device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
   const int r = row0 + 4 * g + (i >> 2), col = col0 + 4 * (i & 3);
   const bf16x4 lo = lds_read_tr(m + swz<D>(r, col >> 3) + (col & 7));
   const bf16x4 hi = lds_read_tr(m + swz<D>(r + 16, col >> 3) + (col & 7));
@@ -163,14 +163,30 @@ __device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0,
 // bf16 MFMA operand fragment along a row of a swizzled tile: row row0 + (lane % 16), the 8
 // elements starting at column 8 * chunk0 + 8 * (lane / 16).
 template <int D>
-__device__ inline bf16x8 frag_along_row_swz(const __bf16* m, int row0, int chunk0, int lane = threadIdx.x & 63) {
+__device__ inline bf16x8 frag_along_row_swz(const __bf16* m, int row0, int chunk0) {
+  const int lane = threadIdx.x & 63;
+  return *reinterpret_cast<const bf16x8*>(m + swz<D>(row0 + (lane & 15), chunk0 + (lane >> 4)));
+}
+
+// The same two with the lane given: a kernel that loops over its work passes one that is opaque in every
+// turn, so that the lane-dependent addresses are not all formed, and spilled, before the loop.
+template <int D>
+__device__ inline bf16x8 frag_down_rows_swz(const __bf16* m, int row0, int col0, int lane) {
+  const int g = lane >> 4, i = lane & 15;
+  const int r = row0 + 4 * g + (i >> 2), col = col0 + 4 * (i & 3);
+  const bf16x4 lo = lds_read_tr(m + swz<D>(r, col >> 3) + (col & 7));
+  const bf16x4 hi = lds_read_tr(m + swz<D>(r + 16, col >> 3) + (col & 7));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+template <int D>
+__device__ inline bf16x8 frag_along_row_swz(const __bf16* m, int row0, int chunk0, int lane) {
   return *reinterpret_cast<const bf16x8*>(m + swz<D>(row0 + (lane & 15), chunk0 + (lane >> 4)));
 }
 
 // As frag_along_row_swz with the k slots in the order of frag_down_rows (and of two stacked 16 x 16
 // results): row row0 + (lane % 16), columns k0 + 4g + {0..3} (slots 0-3), k0 + 16 + 4g + {0..3} (4-7).
 template <int D>
-__device__ inline bf16x8 frag_along_row_perm(const __bf16* m, int row0, int k0, int lane = threadIdx.x & 63) {
+__device__ inline bf16x8 frag_along_row_perm(const __bf16* m, int row0, int k0, int lane) {
   const int g = lane >> 4, r = row0 + (lane & 15), c = (k0 >> 3) + (g >> 1);
   const bf16x4 lo = *reinterpret_cast<const bf16x4*>(m + swz<D>(r, c) + 4 * (g & 1));
   const bf16x4 hi = *reinterpret_cast<const bf16x4*>(m + swz<D>(r, c + 2) + 4 * (g & 1));
