@@ -773,6 +773,19 @@ __device__ inline bf16x8 load_rl_pair(const __bf16* row, int st) {
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// Operand reads of k_bwd_dkv_fast: with OPAQUE (its loop over heads) from the lane given, see
+// frag_down_rows_swz.
+template <int D, bool OPAQUE>
+__device__ inline bf16x8 fr_down(const __bf16* m, int row0, int col0, int lane) {
+  if constexpr (OPAQUE) return frag_down_rows_swz<D>(m, row0, col0, lane);
+  else return frag_down_rows_swz<D>(m, row0, col0);
+}
+template <int D, bool OPAQUE>
+__device__ inline bf16x8 fr_along(const __bf16* m, int row0, int chunk0, int lane) {
+  if constexpr (OPAQUE) return frag_along_row_swz<D>(m, row0, chunk0, lane);
+  else return frag_along_row_swz<D>(m, row0, chunk0);
+}
+
 }  // namespace
 
 template <int DK, int DV>
@@ -1059,12 +1072,18 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dq_fast(
   }
 }
 
-template <int DK, int DV>
+// GROUP (query/key heads shared by groups of heads): a workgroup takes HN heads of one group in turn and sums
+// their dk in its fp32 accumulators, so that one row of dk leaves per HN heads instead of one per head:
+// [B * T][H / HN] rows, the output itself when HN is the whole group, otherwise scratch for
+// k_group_sum.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
+// k_group_sum -> 751 + 8.  (The dq kernel gains nothing from it: its accumulators, live across the heads,
+// spill, and it took 829 us instead of 675 + 79.)
+template <int DK, int DV, bool GROUP>
 __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lam, Nodes<__bf16> nodes, RevNodes<__bf16> rev,
     const float* __restrict__ qdq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, float* __restrict__ dla,
-    float* __restrict__ tsum, int64_t Tlen, int H, int Hqk, int L, int J) {
+    float* __restrict__ tsum, int64_t Tlen, int H, int Hqk, int L, int J, int HN) {
   using M = Mfma<__bf16>;
   typedef __bf16 bf;
   typedef typename M::frag frag;
@@ -1082,17 +1101,28 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
   const int64_t N = (Tlen + R - 1) / R;
   const int64_t work = xcd_remap(blockIdx.x, (int64_t)gridDim.x);  // logical order (b, h, u)
   const int u = (int)(work % N);
-  const int64_t bh = work / N;
-  const int h = (int)(bh % H), b = (int)(bh / H);
-  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int HP = GROUP ? H / HN : H;  // workgroups per sequence and tile: blocks of HN heads
+  const int64_t bp = work / N;
+  const int hp = (int)(bp % HP), b = (int)(bp / HP);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int64_t row0 = (int64_t)b * Tlen + (int64_t)u * R;
   const int nrow = (int)((Tlen - (int64_t)u * R) < R ? (Tlen - (int64_t)u * R) : R);
   const int gA = wave, gB = 7 - wave;            // this wave's 16-key groups
-  const int jA = 16 * gA + r16, jB = 16 * gB + r16;
   const bool liveB = 16 * gB < nrow;
+  const int hq = (GROUP ? hp * HN : hp) / (H / Hqk);  // the heads' query/key head
+  f32x4 akA[MTK], akB[MTK], avA[MTV], avB[MTV];
+  if constexpr (GROUP) {
+#pragma unroll
+    for (int mt = 0; mt < MTK; ++mt) akA[mt] = akB[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  float kdA0 = 0.f, kdB0 = 0.f;  // GROUP: k . dk summed over the heads so far
+  auto head = [&](const int hx, const int tid) __attribute__((always_inline)) {
+  const int lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int jA = 16 * gA + r16, jB = 16 * gB + r16;
+  const int h = GROUP ? hp * HN + hx : hp;
+  const int64_t bh = (int64_t)b * H + h;
   const int64_t growA = (row0 + jA) * H + h, growB = (row0 + (liveB ? jB : 0)) * H + h;
-  const int hq = h / (H / Hqk);  // this head's query/key head
+  if (GROUP && hx) __syncthreads();  // every wave is done with the last head's LDS
   const int64_t kqA = (row0 + jA) * Hqk + hq, kqB = (row0 + (liveB ? jB : 0)) * Hqk + hq;
 
   lds_gather4<NT>(cl_s, R, [&](int x) { return nodes.cl + (bh * N + u) * R + x; });
@@ -1143,9 +1173,10 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     for (int st = 0; st < KSV; ++st) wB_[st] = frag{};
   }
 
-  f32x4 akA[MTK], akB[MTK], avA[MTV], avB[MTV];
+  if constexpr (!GROUP) {
 #pragma unroll
-  for (int mt = 0; mt < MTK; ++mt) akA[mt] = akB[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MTK; ++mt) akA[mt] = akB[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll
   for (int mt = 0; mt < MTV; ++mt) avA[mt] = avB[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -1164,7 +1195,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       f32x4 tA = {0.f, 0.f, 0.f, 0.f}, tB = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int st = 0; st < KSV; ++st) {
-        const frag df = frag_down_rows_swz<DK>(cur, 32 * st, 16 * mt);
+        const frag df = fr_down<DK, GROUP>(cur, 32 * st, 16 * mt, lane);
         tA = M::mma(df, wA_[st], tA);
         tB = M::mma(df, wB_[st], tB);
       }
@@ -1177,7 +1208,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       f32x4 tA = {0.f, 0.f, 0.f, 0.f}, tB = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KSK; ++ks) {
-        const frag df = frag_along_row_swz<DK>(cur, 16 * mt, 4 * ks);
+        const frag df = fr_along<DK, GROUP>(cur, 16 * mt, 4 * ks, lane);
         tA = M::mma(df, kA[ks], tA);
         tB = M::mma(df, kB[ks], tB);
       }
@@ -1239,13 +1270,13 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       f32x4 sA = {0.f, 0.f, 0.f, 0.f}, sB = sA, gA_ = sA, gB_ = sA;
 #pragma unroll
       for (int ks = 0; ks < KSK; ++ks) {
-        const frag f = frag_along_row_swz<DK>(q_s, 16 * QT, 4 * ks);
+        const frag f = fr_along<DK, GROUP>(q_s, 16 * QT, 4 * ks, lane);
         if (useA) sA = M::mma(f, kA[ks], sA);
         if (useB) sB = M::mma(f, kB[ks], sB);
       }
 #pragma unroll
       for (int ks = 0; ks < KSV; ++ks) {
-        const frag f = frag_along_row_swz<DV>(o_s, 16 * QT, 4 * ks);
+        const frag f = fr_along<DV, GROUP>(o_s, 16 * QT, 4 * ks, lane);
         if (useA) gA_ = M::mma(f, vA[ks], gA_);
         if (useB) gB_ = M::mma(f, vB[ks], gB_);
       }
@@ -1254,13 +1285,13 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     }
 #pragma unroll
     for (int mt = 0; mt < MTK; ++mt) {
-      const frag qd = frag_down_rows_swz<DK>(q_s, 32 * st, 16 * mt);
+      const frag qd = fr_down<DK, GROUP>(q_s, 32 * st, 16 * mt, lane);
       if (needA) akA[mt] = M::mma(qd, bgA, akA[mt]);
       if (needB) akB[mt] = M::mma(qd, bgB, akB[mt]);
     }
 #pragma unroll
     for (int mt = 0; mt < MTV; ++mt) {
-      const frag od = frag_down_rows_swz<DV>(o_s, 32 * st, 16 * mt);
+      const frag od = fr_down<DV, GROUP>(o_s, 32 * st, 16 * mt, lane);
       if (needA) avA[mt] = M::mma(od, bpA, avA[mt]);
       if (needB) avB[mt] = M::mma(od, bpB, avB[mt]);
     }
@@ -1285,8 +1316,12 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
   kdA = sum_over_groups(kdA);
   kdB = sum_over_groups(kdB);
   if (g == 0) {
-    dc_s[jA] = qdqA - kdA;
-    dc_s[jB] = liveB ? qdqB - kdB : 0.f;
+    dc_s[jA] = qdqA - (GROUP ? kdA - kdA0 : kdA);
+    dc_s[jB] = liveB ? qdqB - (GROUP ? kdB - kdB0 : kdB) : 0.f;
+  }
+  if constexpr (GROUP) {
+    kdA0 = kdA;
+    kdB0 = kdB;
   }
   __syncthreads();  // every wave is done with Q and dO; dc visible
   // ---- dk and dv through LDS as whole rows
@@ -1308,8 +1343,10 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       *reinterpret_cast<bf16x4*>(o_s + swz<DV>(i, 2 * mt + (g >> 1)) + 4 * (g & 1)) = val;
     }
   };
-  stage_k(akA, jA);
-  stage_k(akB, jB);
+  if (!GROUP || hx == HN - 1) {
+    stage_k(akA, jA);
+    stage_k(akB, jB);
+  }
   stage_v(avA, jA);
   stage_v(avB, jB);
   // suffix sums of dcum within the tile: thread x < R (two waves) scans row R - 1 - x
@@ -1323,12 +1360,14 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     if (row < nrow) dla[(row0 + row) * H + h] = x;
     if (tid == R - 1) tsum[bh * N + u] = x;
   }
+  if (!GROUP || hx == HN - 1) {
 #pragma unroll
   for (int it = 0; it < R * (DK / 8) / NT; ++it) {
     const int idx = it * NT + tid, r = idx / (DK / 8), c = idx % (DK / 8);
     if (r < nrow)
-      *reinterpret_cast<bf16x8*>(dk + ((row0 + r) * H + h) * DK + 8 * c) =
+      *reinterpret_cast<bf16x8*>(dk + ((row0 + r) * HP + hp) * DK + 8 * c) =
           *reinterpret_cast<const bf16x8*>(q_s + swz<DK>(r, c));
+  }
   }
 #pragma unroll
   for (int it = 0; it < R * (DV / 8) / NT; ++it) {
@@ -1336,6 +1375,16 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     if (r < nrow)
       *reinterpret_cast<bf16x8*>(dv + ((row0 + r) * H + h) * DV + 8 * c) =
           *reinterpret_cast<const bf16x8*>(o_s + swz<DV>(r, c));
+  }
+  };
+  if constexpr (GROUP) {
+    for (int hx = 0; hx < HN; ++hx) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));  // opaque in every turn (see frag_down_rows_swz)
+      head(hx, tid);
+    }
+  } else {
+    head(0, threadIdx.x);
   }
 }
 
@@ -1394,23 +1443,35 @@ __global__ __launch_bounds__(256) void k_bwd_dgate(const float* __restrict__ tsu
 // Host side
 // ---------------------------------------------------------------------------------------------
 // ---------------------------------------------------------------------------------------------
-// k_group_sum: heads sharing one query/key head -- out[b, t, hq, :] = sum over the group's heads h
-// of in[b, t, h, :] (fp32 sums of the per-head gradients).  grid (ceil(rows * Hqk * D / 256)).
+// k_group_sum: heads sharing one query/key head -- out[b, t, hq, :] = sum over the group's P / Hqk rows of
+// in [b, t, P, :] (fp32 sums; a row is the gradient of one head, or of a block of heads).  One 16-byte
+// piece per thread, grid (ceil(rows * Hqk * D / pieces / 256)).  Bound: reading `in`; one 2-byte element per
+// thread took 196 us for 805 MB, a piece 79.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void k_group_sum(const T* __restrict__ in, T* __restrict__ out, int64_t rows, int H,
+__global__ __launch_bounds__(256) void k_group_sum(const T* __restrict__ in, T* __restrict__ out, int64_t rows, int P,
                                                    int Hqk, int D) {
+  typedef typename Vec16<T>::type vec;
+  constexpr int V = Vec16<T>::N;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= rows * Hqk * D) return;
-  const int d = (int)(idx % D);
-  const int64_t rq = idx / D;  // (row, hq)
-  const int hq = (int)(rq % Hqk);
-  const int64_t row = rq / Hqk;
-  const int G = H / Hqk;
-  const T* src = in + (row * H + (int64_t)hq * G) * D + d;
-  float acc = 0.f;
-  for (int x = 0; x < G; ++x) acc += to_f32(src[(int64_t)x * D]);
-  out[idx] = from_f32<T>(acc);
+  const int DP = D / V;
+  if (idx >= rows * Hqk * DP) return;
+  const int64_t rq = idx / DP;  // (row, hq): its rows are P / Hqk consecutive ones
+  const int G = P / Hqk;
+  const T* src = in + rq * G * D + (idx % DP) * V;
+  float acc[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] = 0.f;
+#pragma unroll 4
+  for (int x = 0; x < G; ++x) {
+    const vec y = *reinterpret_cast<const vec*>(src + (int64_t)x * D);
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] += to_f32(y[e]);
+  }
+  vec res;
+#pragma unroll
+  for (int e = 0; e < V; ++e) res[e] = from_f32<T>(acc[e]);
+  *reinterpret_cast<vec*>(out + idx * V) = res;
 }
 
 int64_t mamba2_bwd_workspace(int64_t B, int64_t T, int64_t H, int64_t Hqk, int64_t dk, int64_t dv, int64_t C,
@@ -1478,9 +1539,18 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
   const int J = w.fwd.J;
   const int64_t BH = a.B * a.H;
   const bool grouped = a.Hqk < a.H;
-  // per-head dq, dk: the outputs themselves, or scratch summed over each group of heads at the end
+  constexpr bool kFast = std::is_same<T, __bf16>::value && R == kBwdFastRows;
+  // heads per workgroup of the dk, dv kernel with shared query/key heads: the most that divide a group and
+  // leave 1024 workgroups (two per resident one; H_qk = 4 of 32 heads, T = 8192: 215 us at 1024,
+  // 221 at 2048; the shape above 767, 772, and 861 at 6144)
+  int HN = 1;
+  if (kFast && grouped)
+    for (int64_t n = 2, G = a.H / a.Hqk; n <= G; ++n)
+      if (G % n == 0 && w.fwd.N * a.B * (a.H / n) >= 1024) HN = (int)n;
+  const int64_t HP = a.H / HN;  // rows of dk per token
+  // per-head dq, HP rows of dk: the outputs themselves, or scratch summed over each group at the end
   T* dqh = grouped ? reinterpret_cast<T*>(base + w.dqh) : (T*)a.dq;
-  T* dkh = grouped ? reinterpret_cast<T*>(base + w.dkh) : (T*)a.dk;
+  T* dkh = HP > a.Hqk ? reinterpret_cast<T*>(base + w.dkh) : (T*)a.dk;
 
   Mamba2Args fa{};
   fa.q = a.q; fa.k = a.k; fa.v = a.v; fa.log_alpha = a.log_alpha; fa.lambda = a.lambda; fa.o = nullptr;
@@ -1506,7 +1576,6 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
   }
   if (ev) (void)hipEventRecord(ev[2], st);
   const dim3 gtile((unsigned)(w.fwd.N * BH));
-  constexpr bool kFast = std::is_same<T, __bf16>::value && R == kBwdFastRows;
   if constexpr (kFast)
     hipLaunchKernelGGL((k_bwd_dq_fast<DK, DV>), gtile, dim3(kBwdFastThreads), 0, st, (const T*)a.q, (const T*)a.k,
                        (const T*)a.v, (const T*)a.dout, a.lambda, nodes, dqh, a.dlambda, qdq, a.T, (int)a.H,
@@ -1516,21 +1585,23 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
                        (const T*)a.v, (const T*)a.dout, a.log_alpha, a.lambda, nodes, dqh, a.dlambda, qdq, a.T,
                        (int)a.H, (int)a.Hqk, a.L, J);
   if (ev) (void)hipEventRecord(ev[3], st);
-  if constexpr (kFast)
-    hipLaunchKernelGGL((k_bwd_dkv_fast<DK, DV>), gtile, dim3(kBwdFastThreads), 0, st, (const T*)a.q, (const T*)a.k,
-                       (const T*)a.v, (const T*)a.dout, a.lambda, nodes, rev, (const float*)qdq, dkh, (T*)a.dv,
-                       a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J);
+  if constexpr (kFast) {
+    auto* kernel = HN > 1 ? &k_bwd_dkv_fast<DK, DV, true> : &k_bwd_dkv_fast<DK, DV, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(w.fwd.N * a.B * HP)), dim3(kBwdFastThreads), 0, st, (const T*)a.q,
+                       (const T*)a.k, (const T*)a.v, (const T*)a.dout, a.lambda, nodes, rev, (const float*)qdq, dkh, (T*)a.dv,
+                       a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J, HN);
+  }
   else
     hipLaunchKernelGGL((k_bwd_dkv<T, C, DK, DV>), gtile, dim3(4 * R), 0, st, (const T*)a.q, (const T*)a.k,
                        (const T*)a.v, (const T*)a.dout, a.log_alpha, a.lambda, rev, (const float*)qdq, dkh,
                        (T*)a.dv, a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J);
-  if (grouped) {
-    const int64_t n = a.B * a.T * a.Hqk * DK;
-    hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)dqh, (T*)a.dq,
-                       a.B * a.T, (int)a.H, (int)a.Hqk, DK);
-    hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)dkh, (T*)a.dk,
-                       a.B * a.T, (int)a.H, (int)a.Hqk, DK);
-  }
+  auto group_sum = [&](const T* in, void* out, int64_t P) {
+    const int64_t n = a.B * a.T * a.Hqk * DK / Vec16<T>::N;
+    hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, in, (T*)out, a.B * a.T,
+                       (int)P, (int)a.Hqk, DK);
+  };
+  if (grouped) group_sum(dqh, a.dq, a.H);
+  if (HP > a.Hqk) group_sum(dkh, a.dk, HP);
   const uint64_t* tag = a.reuse_summaries ? reinterpret_cast<const uint64_t*>(base + w.fwd.tag) : nullptr;
   hipLaunchKernelGGL((k_bwd_dgate<T, DK, DV>), dim3((unsigned)((a.T + 255) / 256), (unsigned)BH), dim3(256), 0, st,
                      (const float*)tsum, a.dlog_alpha, a.T, (int)a.H, R, tag, mamba2_tag(fa, sizeof(T), true),

@@ -1,0 +1,39 @@
+"""The backward with shared query/key heads at sizes where one workgroup takes a block of heads (at least
+1024 workgroups left): against the backward on q and k repeated to every head, its dq and dk summed over
+each group.  Every head's dq and dk is rounded to bf16 there (relative 2^-9 each) and the sums here
+once, so the two differ by at most about 1e-2 of the largest entry; dv, dlog_alpha and dlambda share their
+arithmetic up to the order of fp32 sums (dlog_alpha: differences of running sums)."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64), (128, 128)])
+@pytest.mark.parametrize("B,H,Hqk,T", [
+    (2, 64, 2, 2112),   # 17 tiles, the last half full: blocks of 2 of 32 heads, summed at the end
+    (2, 64, 32, 2112),  # the block is the whole group: dk written directly
+    (1, 96, 1, 4096),   # blocks of 3 heads
+])
+def test_head_blocks_match_repeated_heads(B, H, Hqk, T, dk, dv):
+    import torch
+    import paper_2506_04761_amd as ll
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = torch.Generator(device="cuda").manual_seed(T + H + Hqk)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    G = H // Hqk
+    q, k = ((rnd(B, T, Hqk, dk) / dk ** 0.5).bfloat16() for _ in range(2))
+    v, do = (rnd(B, T, H, dv) / dv ** 0.5).bfloat16(), rnd(B, T, H, dv).bfloat16()
+    la = -torch.nn.functional.softplus(rnd(B, T, H) - 3)
+    lam = torch.nn.functional.softplus(rnd(B, T, H, ll.ll_num_levels(T)))
+    got = ll.ll_mamba2_bwd(q, k, v, la, lam, do, 64)
+    rep = lambda x: x.repeat_interleave(G, dim=2)
+    ref = ll.ll_mamba2_bwd(rep(q), rep(k), v, la, lam, do, 64)
+    fold = lambda x: x.double().reshape(B, T, Hqk, G, dk).sum(3)
+    for name, a, b, tol in (("dq", got[0], fold(ref[0]), 1e-2), ("dk", got[1], fold(ref[1]), 1e-2),
+                            ("dv", got[2], ref[2].double(), 1e-6), ("dlog_alpha", got[3], ref[3].double(), 1e-3),
+                            ("dlambda", got[4], ref[4].double(), 1e-6)):
+        err = float((a.double() - b).abs().max() / b.abs().max())
+        print(f"{name}: {err:.2e}", flush=True)
+        assert err <= tol, (name, err)
