@@ -673,55 +673,44 @@ def main_bwd(args, w, torch, ll):
 def gdn_issued(w, has_lambda=True):
     """MFMA FLOPs the GDN kernels issue, counted from their loop structure, and the algorithmic
     bytes of the whole call.
-    gdn_chunk, per chunk: K K^T, Q K^T (C x C x d_k), W = T_G (gamma K), Q~ correction (C x d_k x C),
-    U = T_G V, intra output (C x d_v x C), P_G T_G (C x C x C), P_z (d_k x d_k x C), H_z (d_k x d_v x C).
-    Block tree, per block of levels 1 .. J-1: T_hi T_lo (d_k x d_k x d_k) and T_hi A_lo
-    (d_k x d_v x d_k).  Read-out, per chunk and set bit of its index: q~ A (C x d_v x d_k) and, when
+    gdn_pair, per chunk: K K^T, Q K^T (C x C x d_k), W = T_G (gamma K), Q~ correction (C x d_k x C),
+    U = T_G V, intra output (C x d_v x C), P_G T_G (C x C x C), P (d_k x d_k x C), H (d_k x d_v x C); per
+    full pair, for W and for Q~ of its second chunk: the product with the first chunk's keys (C x C x d_k)
+    and that with its W (C x d_k x C) and U (C x d_v x C).
+    Block tree over pairs, per block of levels 1 .. J-1: T_hi T_lo (d_k x d_k x d_k) and T_hi A_lo
+    (d_k x d_v x d_k).  Read-out, per chunk and set bit of its pair's index: q~ A (C x d_v x d_k) and, when
     a higher set bit follows, q~ T (C x d_k x d_k).  lambda == NULL issues the same work."""
     C, dk, dv = w.C, w.dk, w.dv
     N = w.T // C
-    J = (N - 1).bit_length() if N > 1 else 0
+    N2 = (N + 1) // 2
+    J = (N2 - 1).bit_length() if N2 > 1 else 0
     f_chunk = 2.0 * (3 * C * C * dk + C * C * dk + 2 * C * C * dv + C ** 3 + dk * dk * C + dk * dv * C)
-    f_tree = sum((N >> m) * 2.0 * dk * dk * (dk + dv) for m in range(1, J))
+    f_pair = 2.0 * 2 * (2 * C * C * dk + C * C * dv)
+    f_tree = sum((N2 >> m) * 2.0 * dk * dk * (dk + dv) for m in range(1, J))
     f_read = 0.0
     for z in range(N):
-        nb = bin(z).count("1")
+        nb = bin(z >> 1).count("1")
         f_read += nb * 2.0 * C * dk * dv + max(nb - 1, 0) * 2.0 * C * dk * dk
     BH = w.B * w.H
     es = 2 if w.dtype == "bf16" else 4
     L = w.levels if has_lambda else 0
     nbytes = w.B * w.T * w.H * ((2 * dk + 2 * dv) * es + 8 + 4 * L)
-    return BH * N * f_chunk, BH * (f_tree + f_read), nbytes
+    return BH * (N * f_chunk + N // 2 * f_pair), BH * (f_tree + f_read), nbytes
 
 
-def decode_level_reads(T):
-    """Per token t < T: the number of level states (d_v x d_k, fp32) a decode step reads -- the
-    nonempty levels >= 1 other than the one it overwrites -- following the Sec. 3.2 occupancy
-    (level p+1 filled and levels 1..p emptied at t, p = lssb(t))."""
-    occupied, reads = set(), []
-    for t in range(T):
-        if t == 0:
-            reads.append(0)
-            continue
-        p = (t & -t).bit_length() - 1
-        reads.append(len([lv for lv in occupied if lv != p + 1]))
-        occupied -= set(range(1, p + 1))
-        occupied.add(p + 1)
-    return reads
-
-
-def gdn_decode_level_traffic(T):
-    """Per token t < T of Gated DeltaNet decoding: (level states read, level states written).
-    Every nonempty level >= 1 after the step (bit l-1 of t set) is rewritten; the merged level
-    p+1 (p = lssb(t)) reads the previous levels 1..p, the others read themselves."""
-    out = []
-    for t in range(T):
-        if t == 0:
-            out.append((0, 0))
-            continue
-        p = (t & -t).bit_length() - 1
-        n = bin(t).count("1")
-        out.append((n - 1 + p, n))
+def decode_level_traffic(T, window, gdn=False):
+    """Per token t < T: (level states read, level states written, window rows read) of a decode step.
+    The tokens since the last multiple of `window` are rows of k and v; the levels above them hold
+    tokens where t // window has bits set.  Every step reads the nonempty levels and the window's rows;
+    the step that opens a window reads the levels before it and the full window's rows and writes the
+    merged level (Gated DeltaNet: the full window's transitions applied, every nonempty level)."""
+    out = [(0, 0, 0)]
+    for t in range(1, T):
+        now = bin(t // window).count("1")
+        if t % window:
+            out.append((now, 0, t % window))
+        else:
+            out.append((bin((t - 1) // window).count("1"), now if gdn else 1, window))
     return out
 
 
@@ -776,19 +765,13 @@ def main_decode(args, w, torch, ll):
           file=sys.stderr, flush=True)
     BH = w.B * w.H
     SZ4 = w.dk * w.dv * 4
-    token_bytes = BH * ((2 * w.dk + 2 * w.dv) * 2 + 4 + 4 * L + 2 * (w.dv + w.dk) * 4 + (4 if gdn else 0))
-    if gdn:
-        rw = np.array(gdn_decode_level_traffic(w.T)[w.T - M:], dtype=np.float64)
-        per_step = BH * (rw[:, 0].mean() + rw[:, 1].mean()) * SZ4 + token_bytes
-        note = ("per head: the level states read (the carried levels and the merged level's inputs) and every "
-                "nonempty level rewritten by the delta-rule transition, fp32, means over the timed positions, plus "
-                "the token's inputs and output; states partly served by the 256 MB Infinity Cache")
-    else:
-        reads = decode_level_reads(w.T)[w.T - M:]
-        per_step = BH * (np.mean(reads) + 1) * SZ4 + token_bytes
-        note = ("per head: the nonempty level states read (mean over the timed positions) and the merged one "
-                "written, fp32, plus the token's inputs and output; the states re-read every token are partly "
-                "served by the 256 MB Infinity Cache, so the rate can exceed the HBM peak")
+    token_bytes = BH * ((2 * w.dk + 2 * w.dv) * 2 + 4 + 4 * L + (w.dv + w.dk) * 2 + (4 if gdn else 0))
+    window = 8 if w.dk == 16 else 32  # as the kernels keep it
+    rw = np.array(decode_level_traffic(w.T, window, gdn)[w.T - M:], dtype=np.float64).mean(axis=0)
+    per_step = BH * ((rw[0] + rw[1]) * SZ4 + rw[2] * (w.dk + w.dv) * (2 if w.dtype == "bf16" else 4)) + token_bytes
+    note = ("per head: the nonempty level states read and those written when a window of tokens is merged, fp32, and "
+            "the window's rows of k and v, means over the timed positions, plus the token's inputs and output; "
+            "states re-read every token are partly served by the 256 MB Infinity Cache")
     gbs = per_step / (ms * 1e-3) / 1e9
     name = "Gated DeltaNet" if gdn else "Mamba-2"
     res = {
@@ -870,18 +853,17 @@ def main_gdn(args, w, torch, ll, cpu=True):
           f"lambda=NULL {ms_null:.3f} ms/step", file=sys.stderr, flush=True)
 
     f_chunk, f_scan, nbytes = gdn_issued(w)
-    names = ["gdn_chunk", "gdn_tree_read"]
+    names = ["gdn_pair", "gdn_tree_read"]
     dom = int(np.argmax(stage_ms))
-    # per-stage algorithmic bytes: the chunk kernel reads q, k, v, gates, beta and writes the
-    # per-chunk products (Q~, P_z, H_z bf16, intra output fp32); the block tree and the read-out
+    # per-stage algorithmic bytes: the pair kernel reads q, k, v, gates, beta and writes its products (per
+    # chunk Q~ bf16 and the intra output fp32, per pair P and H bf16); the block tree and the read-out
     # read those and lambda and write o (the tree's own blocks are not counted).
     N = w.T // w.C
-    BHN = w.B * w.H * N
-    prod = BHN * (w.C * w.dk * 2 + w.dk * w.dk * 2 + w.dk * w.dv * 2 + w.C * w.dv * 4)
+    prod = w.B * w.H * (N * (w.C * w.dk * 2 + w.C * w.dv * 4) + (N + 1) // 2 * (w.dk * w.dk + w.dk * w.dv) * 2)
     BTH = w.B * w.T * w.H
     b_chunk = BTH * ((2 * w.dk + w.dv) * 2 + 8) + prod
     b_scan = prod + BTH * (4 * w.levels + w.dv * 2)
-    figs = {"gdn_chunk": (f_chunk, b_chunk), "gdn_tree_read": (f_scan, b_scan)}
+    figs = {"gdn_pair": (f_chunk, b_chunk), "gdn_tree_read": (f_scan, b_scan)}
     roof = roofline(w, *figs[names[dom]], stage_ms[dom])
     F = f_chunk + f_scan
     f_n, s_n, _ = gdn_issued(w, has_lambda=False)
@@ -897,7 +879,7 @@ def main_gdn(args, w, torch, ll, cpu=True):
                    "inputs": "bf16 q/k/v (k L2-normalised), fp32 log-gates, beta and lambda, seeded synthetic"},
         "tflops_issued": F / (ms * 1e-3) / 1e12,
         "mfma_peak_frac": F / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
-        "flop_convention": "MFMA FLOPs issued by gdn_chunk, the block tree and the read-out (see gdn_issued)",
+        "flop_convention": "MFMA FLOPs issued by gdn_pair, the block tree and the read-out (see gdn_issued)",
         "hbm_GBps_algorithmic": nbytes / (ms * 1e-3) / 1e9,
         "gdn_lambda_null": {"ms_per_step": ms_null, "tokens_per_s": w.B * w.T / (ms_null * 1e-3),
                             "tflops_issued": (f_n + s_n) / (ms_null * 1e-3) / 1e12},

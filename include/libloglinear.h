@@ -122,17 +122,16 @@ ll_status ll_mamba2_fwd_grouped(const void* q, const void* k, const void* v, con
                                 void* workspace, size_t workspace_bytes, void* stream);
 
 /* Same computation as ll_mamba2_fwd_grouped (ll_mamba2_fwd for H_qk = H), for measurement:
- * also records the caller's HIP events
- * (hipEvent_t handles passed as void*) on `stream`, events[i] right before kernel stage i and
- * events[3] after the last stage, so that the caller can read each stage's duration with
- * hipEventElapsedTime once the stream has passed them.  Stages of the single-pass path (bf16,
- * C = 64): 0 tile totals of the log-gates, 1 aligned block sums of those totals (nothing up to
- * T = 8192), 2 the tile
- * kernel (states, Fenwick nodes, intra-tile and inter-tile terms).  Stages of the three-kernel
- * path: 0 tile states and the summaries of the lowest three tile levels, 1 scan (the block tree
- * of summaries above them; with lambda == NULL the running state of every tile), 2 tile outputs
- * (intra-tile and inter-tile terms).  Asynchronous like ll_mamba2_fwd.  events
- * == NULL or any events[i] == NULL returns LL_ERR_NULL_ARG; the events stay owned by the caller. */
+ * also records the caller's HIP events (hipEvent_t handles passed as void*) on `stream`, events[i]
+ * right before kernel stage i and events[3] after the last stage, so that the caller can read each
+ * stage's duration with hipEventElapsedTime once the stream has passed them.  Stages of the
+ * single-pass path (bf16, C = 64): 0 tile totals of the log-gates, 1 aligned block sums of those
+ * totals (nothing up to T = 8192), 2 the tile kernel (states, Fenwick nodes, intra-tile and
+ * inter-tile terms).  Stages of the three-kernel path: 0 tile states and the summaries of the lowest
+ * three tile levels, 1 scan (the block tree of summaries above them; with lambda == NULL the running
+ * state of every tile), 2 tile outputs (intra-tile and inter-tile terms).  Asynchronous like
+ * ll_mamba2_fwd.  events == NULL or any events[i] == NULL returns LL_ERR_NULL_ARG; the events stay
+ * owned by the caller. */
 ll_status ll_mamba2_fwd_staged(const void* q, const void* k, const void* v, const float* log_alpha,
                                const float* lambda, void* o, int64_t B, int64_t T, int64_t H,
                                int64_t H_qk, int64_t d_k, int64_t d_v, int64_t C, int32_t dtype,
@@ -309,9 +308,9 @@ ll_status ll_gdn_fwd(const void* q, const void* k, const void* v, const float* l
                      void* workspace, size_t workspace_bytes, void* stream);
 
 /* Same computation as ll_gdn_fwd, for measurement: also records the caller's HIP events (as in
- * ll_mamba2_fwd_staged) on `stream`: events[0] before the per-chunk kernel, events[1] between
- * it and the level stage (the block tree of chunk transitions and states, then the per-chunk
- * read-out), events[2] after that stage.  Asynchronous.  events == NULL or any events[i] == NULL
+ * ll_mamba2_fwd_staged) on `stream`: events[0] before the WY kernel, events[1] between
+ * it and the level stage (the block tree of transitions and states of pairs of chunks, then the
+ * per-chunk read-out), events[2] after that stage.  Asynchronous.  events == NULL or any events[i] == NULL
  * returns LL_ERR_NULL_ARG. */
 ll_status ll_gdn_fwd_staged(const void* q, const void* k, const void* v, const float* log_alpha,
                             const float* beta, const float* lambda, void* o, int64_t B, int64_t T,

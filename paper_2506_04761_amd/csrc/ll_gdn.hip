@@ -27,9 +27,13 @@
 // then q~^T <- q~^T T(G_j).  Every source group is the aligned block (level j-1, index
 // (z >> (j-1)) - 1) of a binary block tree built level by level.
 //
-// Kernels: gdn_chunk (one persistent workgroup per compute unit walking its chunks; per chunk the WY
-// solve in fp32 by a blocked inversion and all chunk-local products on MFMA, bf16 operands with fp32
-// accumulation), gdn_combine (one launch per tree level, one workgroup per block) and gdn_read (one
+// Pairs.  The leaves of the tree are pairs of chunks: level j = 1 is done where the chunks' factors are at
+// hand, and both chunks of a pair read the same nodes above it.  In the kernels below a tree level m
+// therefore covers 2^m pairs, and the last pair of an odd chunk count holds one chunk.
+//
+// Kernels: gdn_pair (one persistent workgroup per compute unit walking its pairs; per chunk the WY solve
+// in fp32 by a blocked inversion, all products on MFMA, bf16 operands with fp32 accumulation),
+// gdn_combine (one launch per tree level, one workgroup per block and column group) and gdn_read (one
 // workgroup per chunk: the level read-out and the final output).
 #include <type_traits>
 
@@ -72,6 +76,14 @@ __device__ inline int kfrag_idx(int k, int n) {
 // lane % 16) is, packed to bf16, an operand of the next one, its k slots in the order of
 // frag_down_rows.  LDS per half: K, Q, V (row-major, swizzled; direct loads), T_G, and the fp32 blocks of
 // L and of the inverse, whose room W takes after the inversion; U takes Q's.
+//
+// B = 2, H = 16, T = 8192, d = 128: this kernel 184-190 us where the kernel working on single chunks took
+// 200-224, and the tree level of 79 us over the chunks, with its 403 MB, is gone; the read-out has one node
+// round trip less for half the chunks (160 -> 137 us); the forward 513 -> 396 us.  Bound: bursts of memory
+// traffic at one workgroup per compute unit (stamps: of 51 thousand cycles per pair 13 to 20 thousand wait for
+// staging or behind stores; the fp32 output between kernels is the largest item, 64 KB per pair), then the
+// serial inversion.  A sequence of two chunks has half the workgroups: T = 128, 8 heads, d = 64 takes 15.6 us
+// where single chunks took 14.3; from 16 chunks on pairs win (T = 2048: 32.0 -> 31.3 us).
 // ---------------------------------------------------------------------------------------------
 template <int DK, int DV>
 struct PairHalf {  // LDS of one half
@@ -565,12 +577,12 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 2: one level m >= 1 of the block tree.  Block (m, k) of a sequence covers chunks
+// Kernel 2: one level m >= 1 of the block tree.  Block (m, k) of a sequence covers pairs of chunks
 // [k 2^m, (k + 1) 2^m).  It is formed from blocks lo = 2k and hi = 2k + 1 of level m - 1:
 // T = T_hi T_lo, A = T_hi A_lo + A_hi, fp32 accumulation, one RNE cast.  Storage of a block:
 // T (DK x DK) then A (DK x DV), A in the kfrag layout, T in the kfrag layout when k is even (the
 // source groups that chunks read, and the lo side of the next level) and row-major when k is odd
-// (the hi side).  Level 0 is the chunk kernel's P_z and H_z (same layout rule, by chunk parity).
+// (the hi side).  Level 0 is the pair kernel's P and H (same layout rule, by pair parity).
 // The (DK + DV) / 16 column tiles of [T | A] are split over workgroups of kCombineTiles column
 // tiles, which the dispatch-order remap keeps on one XCD; wave w forms rows 16 (RT w + i) + 0..15
 // of its workgroup's tiles (RT = DK / 64).  An odd block's T is formed transposed
@@ -676,13 +688,17 @@ __device__ __host__ inline int64_t tree_level_offset(int64_t BH, int64_t N, int 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 3: read-out.  One workgroup (4 waves) per chunk z.  The chunk's Q~ rows are carried
-// through its source groups from the lowest set bit of z up: at level j (bit j - 1 set) the rows
-// add lambda_t^(log2 C + j) q~_t^T A(G_j) and, if a higher bit follows, become q~^T T(G_j).  The
+// Kernel 3: read-out.  One workgroup (4 waves) per chunk z.  The chunk's Q~ rows (already through its
+// pair's first chunk) are carried through its source groups from the lowest set bit of z >> 1 up: at level
+// j >= 2 (bit j - 1 of z set) the rows add lambda_t^(log2 C + j) q~_t^T A(G_j) and, if a higher bit follows,
+// become q~^T T(G_j).  The
 // node fragments come straight from global memory in the kfrag layout; Q~ lives in LDS (double
 // buffered, bf16); wave w owns the output columns DV/4 w .. and the Q~ columns DK/4 w .. .  The
 // chunk's intra-chunk output is added at the end and the rows are stored through LDS.
 // lambda == NULL: every level weight is 1 (Gated DeltaNet: the whole prefix state).
+// Bound: one node round trip per level, 3 levels per chunk at T = 8192.  8 waves per pair of chunks, each node
+// read once for both, one column tile per wave: tree and read-out 216 -> 264 us at T = 8192, d = 128 (two
+// workgroups per compute unit with half the loads in flight, and spills).
 // ---------------------------------------------------------------------------------------------
 template <int C, int DK, int DV, bool HAS_LAMBDA>
 __global__ __launch_bounds__(256, 2) void k_gdn_read(const float* __restrict__ lam, const bf* __restrict__ qc_in,

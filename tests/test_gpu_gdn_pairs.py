@@ -1,0 +1,38 @@
+"""Log-linear Gated DeltaNet by pairs of chunks (the unit of the WY kernel, the tree and the read-out) where
+pairs can go wrong: an odd chunk count leaves the last pair half full, and more pairs than compute units
+give the persistent workgroups a second turn for some of them.  Sampled heads against the float64
+quadratic form; bf16 inputs with fp32 accumulation, normalised max-abs error <= 2e-2 as for the forward."""
+
+import numpy as np
+import pytest
+
+from oracle import gdn
+from synthetic import WORKLOADS, generate
+from tests.gpu_util import rel_err, run_gdn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,H,chunks", [
+    (1, 300, 1),  # half-full pairs only, 300 of them on 256 compute units
+    (2, 70, 3),   # 280 pairs: full and half-full ones in turn
+    (3, 40, 5),   # 360 pairs, a tree of one level over an odd pair count
+    (1, 90, 6),   # 270 full pairs
+])
+@pytest.mark.parametrize("with_lambda", [True, False])
+def test_pairs(d, B, H, chunks, with_lambda):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = WORKLOADS["ll_gdn_bf16_T8192"].with_(B=B, H=H, T=64 * chunks, dk=d, dv=d, dist="gdn_slow", seed=700 + H)
+    x = generate(w)
+    got = run_gdn(x, 64, with_lambda=with_lambda)
+    assert np.isfinite(got).all()
+    for h in (0, H // 2, H - 1):
+        y = {n: a[:, :, h:h + 1] for n, a in x.items()}
+        lam = y["lam"] if with_lambda else np.ones_like(y["lam"])
+        ref = gdn.quadratic(y["q"], y["k"], y["v"], y["log_alpha"], y["beta"], lam)
+        err = rel_err(got[:, :, h:h + 1], ref)
+        print(f"GDN pairs d={d} B={B} H={H} chunks={chunks} head {h} lambda={with_lambda}: rel err {err:.3e}", flush=True)
+        assert err <= 2e-2, err
