@@ -1,8 +1,8 @@
 """Decoding at the edges of the token window (the tokens since the last multiple of W = 32, or 8 for
 d = 16, are kept as rows; the step that opens a window merges the last one): states of few levels,
 whose window is shorter than W, sequences around one and several merges, a gate that resets the
-state, the kernels with 64 rows of d_v per workgroup (large batches) and a state copied in the
-middle of a window.  References and bars are those of test_gpu_decode.py and test_gpu_gdn_decode.py:
+state, decays under which levels vanish, the kernels with 64 rows of d_v per workgroup (large batches)
+and a state copied in the middle of a window.  References and bars are those of test_gpu_decode.py and test_gpu_gdn_decode.py:
 the float64 oracle, normalised max error 1e-4 (fp32) and 2e-2 (bf16)."""
 
 import numpy as np
@@ -118,3 +118,19 @@ def test_copied_state(variant):
     fork = dec.state.clone()
     a, b = dec.feed(77, 110, fork), dec.feed(77, 110)
     assert (a == b).all() and rel_err(b, reference(variant, x)[77:]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("dtype,d,rep", [("f32", (16, 16), 1), ("bf16", (128, 128), 1), ("bf16", (128, 128), 400)])
+def test_decayed_levels(dtype, d, rep):
+    """Some heads decay so fast that their higher levels' scales reach zero (which are then not read), others
+    not at all: 600 tokens, every position and head against the oracle."""
+    T = 600
+    x = inputs("mamba2", dtype, d, T)
+    x["log_alpha"][:, :, 0] = -3.0
+    x["log_alpha"][:, :, 1] = 0.0
+    x["log_alpha"][:, 300:, 2] = -1.0  # the first half's levels vanish while the sequence runs
+    got = Decoder("mamba2", x, dtype, fenwick.num_levels(T), rep).feed(0, T).reshape(T, 3, rep, d[1])
+    ref = reference("mamba2", x)
+    for h in range(3):
+        assert rel_err(got[:, h, 0], ref[:, h]) <= TOL[dtype], h
+    assert (got == got[:, :, :1]).all()
