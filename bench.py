@@ -771,7 +771,7 @@ def main_decode(args, w, torch, ll):
     per_step = BH * ((rw[0] + rw[1]) * SZ4 + rw[2] * (w.dk + w.dv) * (2 if w.dtype == "bf16" else 4)) + token_bytes
     note = ("per head: the nonempty level states read and those written when a window of tokens is merged, fp32, and "
             "the window's rows of k and v, means over the timed positions, plus the token's inputs and output; "
-            "states re-read every token are partly served by the 256 MB Infinity Cache")
+            "Mamba-2 levels that have decayed to nothing are counted but not read, and states re-read every token are partly served by the 256 MB Infinity Cache")
     gbs = per_step / (ms * 1e-3) / 1e9
     name = "Gated DeltaNet" if gdn else "Mamba-2"
     res = {
