@@ -1075,7 +1075,8 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dq_fast(
 // GROUP (query/key heads shared by groups of heads): a workgroup takes HN heads of one group in turn and sums
 // their dk in its fp32 accumulators, so that one row of dk leaves per HN heads instead of one per head:
 // [B * T][H / HN] rows, the output itself when HN is the whole group, otherwise scratch for
-// k_group_sum.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
+// k_group_sum.  dlog_alpha stays each head's own: its k . dk comes from the head's weights and dv terms, never
+// as a difference of the shared sums, which would round it at the size of the largest head.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
 // k_group_sum -> 751 + 8.  (The dq kernel gains nothing from it: its accumulators, live across the heads,
 // spill, and it took 829 us instead of 675 + 79.)
 template <int DK, int DV, bool GROUP>
@@ -1115,7 +1116,6 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
 #pragma unroll
     for (int mt = 0; mt < MTK; ++mt) akA[mt] = akB[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float kdA0 = 0.f, kdB0 = 0.f;  // GROUP: k . dk summed over the heads so far
   auto head = [&](const int hx, const int tid) __attribute__((always_inline)) {
   const int lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int jA = 16 * gA + r16, jB = 16 * gB + r16;
@@ -1230,6 +1230,18 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     __syncthreads();
     copy_tile(cur);
   }
+  // GROUP: this head's k . dk, without the dk that the heads share: of the levels v . dv (so far avA, avB hold
+  // their terms alone, sum_n D[p][n] k[n] at the rows p of v), of the tile below bg . S
+  float kdA = 0.f, kdB = 0.f;
+  if constexpr (GROUP) {
+#pragma unroll
+    for (int mt = 0; mt < MTV; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        kdA += avA[mt][r] * static_cast<float>(wA_[mt >> 1][4 * (mt & 1) + r]);
+        kdB += avB[mt][r] * static_cast<float>(wB_[mt >> 1][4 * (mt & 1) + r]);
+      }
+  }
   // v rows along d_v for the intra-tile G (the result-row order copies are no longer needed)
   frag vA[KSV], vB[KSV];
 #pragma unroll
@@ -1245,7 +1257,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
   // weights of query tile QT for one key group from its S and G tiles (result layout: query
   // 16 QT + 4 g + r, key jX), into slots 4 hh + r of the packed B operands
   auto weights = [&](int QT, int gX, int jX, float clX, const f32x4& s, const f32x4& gg, bf16x8& bg, bf16x8& bp,
-                     int hh) {
+                     int hh, float& kd) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = 16 * QT + 4 * g + r;
@@ -1254,6 +1266,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       const float lw = ok ? lam_s[i * kMaxLevels + lv] * fast_exp2(cl_s[i] - clX) : 0.f;
       bg[4 * hh + r] = static_cast<bf>(lw * gg[r]);
       bp[4 * hh + r] = static_cast<bf>(lw * s[r]);
+      if constexpr (GROUP) kd += static_cast<float>(bg[4 * hh + r]) * s[r];  // the rounding that dq and dk take
     }
   };
 #pragma unroll
@@ -1280,8 +1293,8 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
         if (useA) gA_ = M::mma(f, vA[ks], gA_);
         if (useB) gB_ = M::mma(f, vB[ks], gB_);
       }
-      if (useA) weights(QT, gA, jA, clA, sA, gA_, bgA, bpA, hh);
-      if (useB) weights(QT, gB, jB, clB, sB, gB_, bgB, bpB, hh);
+      if (useA) weights(QT, gA, jA, clA, sA, gA_, bgA, bpA, hh, kdA);
+      if (useB) weights(QT, gB, jB, clB, sB, gB_, bgB, bpB, hh, kdB);
     }
 #pragma unroll
     for (int mt = 0; mt < MTK; ++mt) {
@@ -1298,8 +1311,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
   }
 
   // ---- k . dk, dcum = q . dq - k . dk
-  float kdA = 0.f, kdB = 0.f;
-  {
+  if constexpr (!GROUP) {
     const bf* ka = k + kqA * DK + 4 * g;
     const bf* kb = k + kqB * DK + 4 * g;
 #pragma unroll
@@ -1316,12 +1328,8 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
   kdA = sum_over_groups(kdA);
   kdB = sum_over_groups(kdB);
   if (g == 0) {
-    dc_s[jA] = qdqA - (GROUP ? kdA - kdA0 : kdA);
-    dc_s[jB] = liveB ? qdqB - (GROUP ? kdB - kdB0 : kdB) : 0.f;
-  }
-  if constexpr (GROUP) {
-    kdA0 = kdA;
-    kdB0 = kdB;
+    dc_s[jA] = qdqA - kdA;
+    dc_s[jB] = liveB ? qdqB - kdB : 0.f;
   }
   __syncthreads();  // every wave is done with Q and dO; dc visible
   // ---- dk and dv through LDS as whole rows

@@ -2,7 +2,7 @@
 1024 workgroups left): against the backward on q and k repeated to every head, its dq and dk summed over
 each group.  Every head's dq and dk is rounded to bf16 there (relative 2^-9 each) and the sums here
 once, so the two differ by at most about 1e-2 of the largest entry; dv, dlog_alpha and dlambda share their
-arithmetic up to the order of fp32 sums (dlog_alpha: differences of running sums)."""
+arithmetic up to the order of fp32 sums (dlog_alpha: suffix sums of differences that nearly cancel)."""
 
 import pytest
 
@@ -37,3 +37,45 @@ def test_head_blocks_match_repeated_heads(B, H, Hqk, T, dk, dv):
         err = float((a.double() - b).abs().max() / b.abs().max())
         print(f"{name}: {err:.2e}", flush=True)
         assert err <= tol, (name, err)
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64), (128, 128)])
+@pytest.mark.parametrize("B,H,Hqk,T", [
+    (8, 64, 1, 2112),  # blocks of 8 heads, the last tile half full
+    (1, 96, 1, 4096),  # blocks of 3 heads
+])
+def test_heads_of_a_block_are_independent(B, H, Hqk, T, dk, dv):
+    """dv, dlog_alpha and dlambda belong to one head: what a head of its block holds, be it 1e5 times as
+    large or not finite, does not change a bit of the others'.  And each head's dlog_alpha, of scales
+    from 1 to 1e4 within a block, against the backward that gives every head its own workgroup, on the
+    head's own scale.  The two sum the same bf16 products in another order, so each term of a suffix sum
+    differs by some 2^-23 of its parts q . dq and k . dk: up to 2^-23 sqrt(4096) = 8e-6 of the parts, which
+    are a few times dlog_alpha's largest entry at most (seen: 4e-6 of that)."""
+    import torch
+    import paper_2506_04761_amd as ll
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = torch.Generator(device="cuda").manual_seed(T + H + dv)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k = ((rnd(B, T, Hqk, dk) / dk ** 0.5).bfloat16() for _ in range(2))
+    v, do = (rnd(B, T, H, dv) / dv ** 0.5).bfloat16(), rnd(B, T, H, dv).bfloat16()
+    la = -torch.exp(torch.linspace(-7, 0, H, device="cuda")) * torch.exp(0.5 * rnd(B, T, H))
+    lam = torch.nn.functional.softplus(rnd(B, T, H, ll.ll_num_levels(T)))
+    loud = torch.arange(H, device="cuda") % 4 == 0
+    base = ll.ll_mamba2_bwd(q, k, v, la, lam, do, 64)
+    for value in ("scaled", "inf", "nan"):
+        d = do.clone()
+        if value == "scaled":
+            d[:, :, loud] *= 1e5
+        else:
+            d[:, T // 3, loud] = float(value)
+        got = ll.ll_mamba2_bwd(q, k, v, la, lam, d, 64)
+        for name, a, b in (("dv", got[2], base[2]), ("dlog_alpha", got[3], base[3]), ("dlambda", got[4], base[4])):
+            assert torch.equal(a[:, :, ~loud], b[:, :, ~loud]), (value, name)
+    d = do * (10.0 ** (torch.arange(H, device="cuda") * 7 % 5))[:, None].bfloat16()
+    got = ll.ll_mamba2_bwd(q, k, v, la, lam, d, 64)[3].double()
+    rep = lambda x: x.repeat_interleave(H // Hqk, dim=2)
+    ref = ll.ll_mamba2_bwd(rep(q), rep(k), v, la, lam, d, 64)[3].double()
+    err = (got - ref).abs().amax(dim=(0, 1)) / ref.abs().amax(dim=(0, 1))
+    print(f"dlog_alpha per head: {float(err.max()):.2e} (head {int(err.argmax())})", flush=True)
+    assert float(err.max()) <= 5e-5
