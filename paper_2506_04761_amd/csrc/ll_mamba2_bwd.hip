@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dq_fast(
 // GROUP (query/key heads shared by groups of heads): a workgroup takes HN heads of one group in turn and sums
 // their dk in its fp32 accumulators, so that one row of dk leaves per HN heads instead of one per head:
 // [B * T][H / HN] rows, the output itself when HN is the whole group, otherwise scratch for
-// k_group_sum.  dlog_alpha stays each head's own: its k . dk comes from the head's weights and dv terms, never
+// k_group_sum (dk32: fp32, no more bytes than one bf16 row per head).  dlog_alpha stays each head's own: its k . dk comes from the head's weights and dv terms, never
 // as a difference of the shared sums, which would round it at the size of the largest head.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
 // k_group_sum -> 751 + 8.  (The dq kernel gains nothing from it: its accumulators, live across the heads,
 // spill, and it took 829 us instead of 675 + 79.)
@@ -1083,8 +1083,8 @@ template <int DK, int DV, bool GROUP>
 __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lam, Nodes<__bf16> nodes, RevNodes<__bf16> rev,
-    const float* __restrict__ qdq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, float* __restrict__ dla,
-    float* __restrict__ tsum, int64_t Tlen, int H, int Hqk, int L, int J, int HN) {
+    const float* __restrict__ qdq, __bf16* __restrict__ dk, float* __restrict__ dk32, __bf16* __restrict__ dv,
+    float* __restrict__ dla, float* __restrict__ tsum, int64_t Tlen, int H, int Hqk, int L, int J, int HN) {
   using M = Mfma<__bf16>;
   typedef __bf16 bf;
   typedef typename M::frag frag;
@@ -1351,7 +1351,16 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
       *reinterpret_cast<bf16x4*>(o_s + swz<DV>(i, 2 * mt + (g >> 1)) + 4 * (g & 1)) = val;
     }
   };
-  if (!GROUP || hx == HN - 1) {
+  if (GROUP && dk32) {
+    if (hx == HN - 1) {
+      float* out = dk32 + (row0 * HP + hp) * DK + 4 * g;
+#pragma unroll
+      for (int mt = 0; mt < MTK; ++mt) {
+        if (jA < nrow) *reinterpret_cast<f32x4*>(out + (int64_t)jA * HP * DK + 16 * mt) = akA[mt];
+        if (jB < nrow) *reinterpret_cast<f32x4*>(out + (int64_t)jB * HP * DK + 16 * mt) = akB[mt];
+      }
+    }
+  } else if (!GROUP || hx == HN - 1) {
     stage_k(akA, jA);
     stage_k(akB, jB);
   }
@@ -1368,7 +1377,7 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     if (row < nrow) dla[(row0 + row) * H + h] = x;
     if (tid == R - 1) tsum[bh * N + u] = x;
   }
-  if (!GROUP || hx == HN - 1) {
+  if (!GROUP || (!dk32 && hx == HN - 1)) {
 #pragma unroll
   for (int it = 0; it < R * (DK / 8) / NT; ++it) {
     const int idx = it * NT + tid, r = idx / (DK / 8), c = idx % (DK / 8);
@@ -1456,25 +1465,29 @@ __global__ __launch_bounds__(256) void k_bwd_dgate(const float* __restrict__ tsu
 // piece per thread, grid (ceil(rows * Hqk * D / pieces / 256)).  Bound: reading `in`; one 2-byte element per
 // thread took 196 us for 805 MB, a piece 79.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_group_sum(const T* __restrict__ in, T* __restrict__ out, int64_t rows, int P,
+template <typename Tin, typename T>
+__global__ __launch_bounds__(256) void k_group_sum(const Tin* __restrict__ in, T* __restrict__ out, int64_t rows, int P,
                                                    int Hqk, int D) {
   typedef typename Vec16<T>::type vec;
-  constexpr int V = Vec16<T>::N;
+  typedef typename Vec16<Tin>::type vin;
+  constexpr int V = Vec16<T>::N, VI = Vec16<Tin>::N;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int DP = D / V;
   if (idx >= rows * Hqk * DP) return;
   const int64_t rq = idx / DP;  // (row, hq): its rows are P / Hqk consecutive ones
   const int G = P / Hqk;
-  const T* src = in + rq * G * D + (idx % DP) * V;
+  const Tin* src = in + rq * G * D + (idx % DP) * V;
   float acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
 #pragma unroll 4
   for (int x = 0; x < G; ++x) {
-    const vec y = *reinterpret_cast<const vec*>(src + (int64_t)x * D);
 #pragma unroll
-    for (int e = 0; e < V; ++e) acc[e] += to_f32(y[e]);
+    for (int c = 0; c < V; c += VI) {
+      const vin y = *reinterpret_cast<const vin*>(src + (int64_t)x * D + c);
+#pragma unroll
+      for (int e = 0; e < VI; ++e) acc[c + e] += to_f32(y[e]);
+    }
   }
   vec res;
 #pragma unroll
@@ -1556,9 +1569,11 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
     for (int64_t n = 2, G = a.H / a.Hqk; n <= G; ++n)
       if (G % n == 0 && w.fwd.N * a.B * (a.H / n) >= 1024) HN = (int)n;
   const int64_t HP = a.H / HN;  // rows of dk per token
-  // per-head dq, HP rows of dk: the outputs themselves, or scratch summed over each group at the end
+  // per-head dq, HP rows of dk: the outputs themselves, or scratch summed over each group at the end (dk of
+  // blocks of heads in fp32: rounding the blocks' sums to bf16 cost as much as rounding dk itself)
   T* dqh = grouped ? reinterpret_cast<T*>(base + w.dqh) : (T*)a.dq;
   T* dkh = HP > a.Hqk ? reinterpret_cast<T*>(base + w.dkh) : (T*)a.dk;
+  float* dk32 = HN > 1 && HP > a.Hqk ? reinterpret_cast<float*>(base + w.dkh) : nullptr;
 
   Mamba2Args fa{};
   fa.q = a.q; fa.k = a.k; fa.v = a.v; fa.log_alpha = a.log_alpha; fa.lambda = a.lambda; fa.o = nullptr;
@@ -1596,20 +1611,22 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
   if constexpr (kFast) {
     auto* kernel = HN > 1 ? &k_bwd_dkv_fast<DK, DV, true> : &k_bwd_dkv_fast<DK, DV, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(w.fwd.N * a.B * HP)), dim3(kBwdFastThreads), 0, st, (const T*)a.q,
-                       (const T*)a.k, (const T*)a.v, (const T*)a.dout, a.lambda, nodes, rev, (const float*)qdq, dkh, (T*)a.dv,
-                       a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J, HN);
+                       (const T*)a.k, (const T*)a.v, (const T*)a.dout, a.lambda, nodes, rev, (const float*)qdq, dkh, dk32,
+                       (T*)a.dv, a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J, HN);
   }
   else
     hipLaunchKernelGGL((k_bwd_dkv<T, C, DK, DV>), gtile, dim3(4 * R), 0, st, (const T*)a.q, (const T*)a.k,
                        (const T*)a.v, (const T*)a.dout, a.log_alpha, a.lambda, rev, (const float*)qdq, dkh,
                        (T*)a.dv, a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J);
-  auto group_sum = [&](const T* in, void* out, int64_t P) {
+  auto group_sum = [&](auto* in, void* out, int64_t P) {
     const int64_t n = a.B * a.T * a.Hqk * DK / Vec16<T>::N;
-    hipLaunchKernelGGL((k_group_sum<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, in, (T*)out, a.B * a.T,
-                       (int)P, (int)a.Hqk, DK);
+    typedef std::remove_pointer_t<decltype(in)> Tin;
+    hipLaunchKernelGGL((k_group_sum<Tin, T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const Tin*)in, (T*)out,
+                       a.B * a.T, (int)P, (int)a.Hqk, DK);
   };
   if (grouped) group_sum(dqh, a.dq, a.H);
-  if (HP > a.Hqk) group_sum(dkh, a.dk, HP);
+  if (dk32) group_sum(dk32, a.dk, HP);
+  else if (HP > a.Hqk) group_sum(dkh, a.dk, HP);
   const uint64_t* tag = a.reuse_summaries ? reinterpret_cast<const uint64_t*>(base + w.fwd.tag) : nullptr;
   hipLaunchKernelGGL((k_bwd_dgate<T, DK, DV>), dim3((unsigned)((a.T + 255) / 256), (unsigned)BH), dim3(256), 0, st,
                      (const float*)tsum, a.dlog_alpha, a.T, (int)a.H, R, tag, mamba2_tag(fa, sizeof(T), true),

@@ -79,3 +79,39 @@ def test_heads_of_a_block_are_independent(B, H, Hqk, T, dk, dv):
     err = (got - ref).abs().amax(dim=(0, 1)) / ref.abs().amax(dim=(0, 1))
     print(f"dlog_alpha per head: {float(err.max()):.2e} (head {int(err.argmax())})", flush=True)
     assert float(err.max()) <= 5e-5
+
+
+@pytest.mark.parametrize("dk,dv", [(128, 64)])
+@pytest.mark.parametrize("B,H,Hqk,T", [
+    (16, 64, 1, 256),  # blocks of 2 heads: 32 rows of dk summed at the end
+    (16, 64, 1, 960),  # blocks of 8 heads, the last tile half full
+])
+def test_dk_is_no_further_from_float64_than_a_sum_of_rounded_heads(B, H, Hqk, T, dk, dv):
+    """dk against float64: summing blocks of heads in fp32 takes roundings to bf16 out, so its error (2-norm)
+    is below that of the sum of every head's dk rounded to bf16."""
+    import torch
+    import paper_2506_04761_amd as ll
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = torch.Generator(device="cuda").manual_seed(T + dv)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k = ((rnd(B, T, Hqk, dk) / dk ** 0.5).bfloat16() for _ in range(2))
+    v, do = (rnd(B, T, H, dv) / dv ** 0.5).bfloat16(), rnd(B, T, H, dv).bfloat16()
+    la = -torch.exp(torch.linspace(-7, 0, H, device="cuda")) * torch.exp(0.5 * rnd(B, T, H))
+    lam = torch.nn.functional.softplus(rnd(B, T, H, ll.ll_num_levels(T)))
+    got = ll.ll_mamba2_bwd(q, k, v, la, lam, do, 64)[1].double()
+    rep = lambda x: x.repeat_interleave(H // Hqk, dim=2)
+    heads = ll.ll_mamba2_bwd(rep(q), rep(k), v, la, lam, do, 64)[1]
+    per_head = heads.float().reshape(B, T, Hqk, H // Hqk, dk).sum(3).bfloat16().double()
+    pos = torch.arange(T, device="cuda")
+    level = torch.frexp((pos[:, None] ^ pos).double())[1].long()
+    exact = torch.zeros_like(got)
+    for h in range(H):
+        cum = la[:, :, h].double().cumsum(1)
+        w = torch.exp((cum[:, :, None] - cum[:, None]).masked_fill(pos[:, None] < pos, -torch.inf))
+        w *= lam[:, :, h].double().gather(2, level.expand(B, -1, -1).clamp(max=lam.shape[-1] - 1))
+        w *= do[:, :, h].double() @ v[:, :, h].double().transpose(1, 2).contiguous()
+        exact[:, :, h // (H // Hqk)] += w.transpose(1, 2).contiguous() @ q[:, :, h // (H // Hqk)].double()
+    err = lambda x: float((x - exact).norm() / exact.norm())
+    print(f"dk: {err(got):.3e}, heads rounded one by one {err(per_head):.3e}", flush=True)
+    assert err(got) < 0.95 * err(per_head)
