@@ -1074,11 +1074,12 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dq_fast(
 
 // GROUP (query/key heads shared by groups of heads): a workgroup takes HN heads of one group in turn and sums
 // their dk in its fp32 accumulators, so that one row of dk leaves per HN heads instead of one per head:
-// [B * T][H / HN] rows, the output itself when HN is the whole group, otherwise scratch for
-// k_group_sum (dk32: fp32, no more bytes than one bf16 row per head).  dlog_alpha stays each head's own: its k . dk comes from the head's weights and dv terms, never
-// as a difference of the shared sums, which would round it at the size of the largest head.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
-// k_group_sum -> 751 + 8.  (The dq kernel gains nothing from it: its accumulators, live across the heads,
-// spill, and it took 829 us instead of 675 + 79.)
+// [B * T][H / HN] rows, the output itself when HN is the whole group, otherwise scratch for k_group_sum
+// (dk32: fp32, no more bytes than one bf16 row per head).  dlog_alpha stays each head's own: its k . dk comes
+// from the head's weights and dv terms, never as a difference of the shared sums, which would round it at
+// the size of the largest head.  B = 2, 48 heads, one query/key head, T = 16384, 128 x 64: 787 us + 79 us of
+// k_group_sum -> 764 + 14, the whole backward 2140 -> 1966.  (The dq kernel gains nothing from it: its
+// accumulators, live across the heads, spill, and it took 829 us instead of 675 + 79.)
 template <int DK, int DV, bool GROUP>
 __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -1561,13 +1562,22 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
   const int64_t BH = a.B * a.H;
   const bool grouped = a.Hqk < a.H;
   constexpr bool kFast = std::is_same<T, __bf16>::value && R == kBwdFastRows;
-  // heads per workgroup of the dk, dv kernel with shared query/key heads: the most that divide a group and
-  // leave 1024 workgroups (two per resident one; H_qk = 4 of 32 heads, T = 8192: 215 us at 1024,
-  // 221 at 2048; the shape above 767, 772, and 861 at 6144)
+  // Heads per workgroup of the dk, dv kernel with shared query/key heads: the most that divide a group and
+  // leave 1024 workgroups, two rounds of the 512 resident ones, whose last round is not nearly empty (the
+  // rounds are at most 1.25 times the work).  Whole backward, 128 x 64, one head per workgroup against n:
+  // B = 2, 48 heads, one query/key head, T = 16384: 2140 / 1966 us at n = 12 (1024 workgroups), 2146 at 16 (768);
+  // 32 heads, H_qk = 4, T = 8192: 719 / 676 (B = 2, n = 4), 1376 / 1243 (B = 4, n = 8); 1032 workgroups of 48
+  // heads, T = 5504: 385 / 392, not taken.  Only where d_k > d_v, so that the dk kept across the heads is what
+  // memory traffic is saved on: with d_k = d_v one head per workgroup is faster nearly everywhere (the first
+  // shape 2930 / 2957 us at 128 x 128, where the loop spills, and 1390 / 1424 at 64 x 64, where it costs the
+  // third wave per SIMD; 64 heads, B = 8, T = 2112: 1802 / 1968 and 870 / 957).
+  constexpr bool kGroup = kFast && DK > DV;
   int HN = 1;
-  if (kFast && grouped)
-    for (int64_t n = 2, G = a.H / a.Hqk; n <= G; ++n)
-      if (G % n == 0 && w.fwd.N * a.B * (a.H / n) >= 1024) HN = (int)n;
+  if (kGroup && grouped)
+    for (int64_t n = 2, G = a.H / a.Hqk; n <= G; ++n) {
+      const int64_t wgs = w.fwd.N * a.B * (a.H / n), rounds = (wgs + 511) / 512;
+      if (G % n == 0 && wgs >= 1024 && 4 * 512 * rounds <= 5 * wgs) HN = (int)n;
+    }
   const int64_t HP = a.H / HN;  // rows of dk per token
   // per-head dq, HP rows of dk: the outputs themselves, or scratch summed over each group at the end (dk of
   // blocks of heads in fp32: rounding the blocks' sums to bf16 cost as much as rounding dk itself)
@@ -1609,7 +1619,8 @@ hipError_t launch_mamba2_bwd(const Mamba2BwdArgs& a, hipStream_t st, hipEvent_t*
                        (int)a.H, (int)a.Hqk, a.L, J);
   if (ev) (void)hipEventRecord(ev[3], st);
   if constexpr (kFast) {
-    auto* kernel = HN > 1 ? &k_bwd_dkv_fast<DK, DV, true> : &k_bwd_dkv_fast<DK, DV, false>;
+    auto* kernel = &k_bwd_dkv_fast<DK, DV, false>;
+    if constexpr (kGroup) kernel = HN > 1 ? &k_bwd_dkv_fast<DK, DV, true> : kernel;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(w.fwd.N * a.B * HP)), dim3(kBwdFastThreads), 0, st, (const T*)a.q,
                        (const T*)a.k, (const T*)a.v, (const T*)a.dout, a.lambda, nodes, rev, (const float*)qdq, dkh, dk32,
                        (T*)a.dv, a.dlog_alpha, tsum, a.T, (int)a.H, (int)a.Hqk, a.L, J, HN);
