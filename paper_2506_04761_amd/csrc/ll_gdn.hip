@@ -233,7 +233,7 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
     const f32x4 ct = *reinterpret_cast<const f32x4*>(&S.cl[16 * i + 4 * g]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float y = bt[r] * acc[r] * fast_exp2(fminf(ct[r] - cs, 0.f));
+      const float y = bt[r] * acc[r] * fast_exp2(ct[r] - cs);
       acc[r] = s < 16 * i + 4 * g + r ? y : 0.f;
     }
     return acc;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
       const f32x4 cs = *reinterpret_cast<const f32x4*>(&S.cl[16 * st + 4 * g]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float y = acc[r] * fast_exp2(fminf(ct - cs[r], 0.f));
+        const float y = acc[r] * fast_exp2(ct - cs[r]);
         acc[r] = 16 * st + 4 * g + r <= t_own ? y : 0.f;
       }
       p4[st] = pack(acc);

@@ -36,3 +36,31 @@ def test_pairs(d, B, H, chunks, with_lambda):
         err = rel_err(got[:, :, h:h + 1], ref)
         print(f"GDN pairs d={d} B={B} H={H} chunks={chunks} head {h} lambda={with_lambda}: rel err {err:.3e}", flush=True)
         assert err <= 2e-2, err
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_gates_above_one_grow(d):
+    """log_alpha > 0 is the caller's to avoid, but is computed like any other: against the oracle, with the
+    growth over the sequence kept within a factor of e^2.6."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = WORKLOADS["ll_gdn_bf16_T8192"].with_(B=1, H=2, T=320, dk=d, dv=d, dist="gdn_slow", seed=31)
+    x = generate(w)
+    x["log_alpha"] = np.abs(np.random.default_rng(d).standard_normal(x["log_alpha"].shape)).astype(np.float32) * 0.01
+    ref = gdn.quadratic(x["q"], x["k"], x["v"], x["log_alpha"], x["beta"], x["lam"])
+    err = rel_err(run_gdn(x, 64), ref)
+    print(f"GDN d={d} growing gates: rel err {err:.3e}", flush=True)
+    assert err <= 2e-2
+
+
+@pytest.mark.parametrize("at", [3, 63, 64, 200])
+def test_nan_gate_reaches_every_later_row(at):
+    """A gate that is not a number makes its token's row and all later ones of the head NaN, and no other head's."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = generate(WORKLOADS["ll_gdn_bf16_T8192"].with_(B=1, H=2, T=320, dk=64, dv=64, dist="gdn_slow", seed=32))
+    x["log_alpha"][0, at, 1] = np.nan
+    o = run_gdn(x, 64)
+    assert np.isnan(o[0, at:, 1]).all() and np.isfinite(o[0, :, 0]).all()
