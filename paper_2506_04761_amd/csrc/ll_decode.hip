@@ -142,6 +142,23 @@ struct DecodeWindow {
   }
 };
 
+// The slot of lane c's u-th token in a window of i tokens, -1 past its end.  Slot i is the step's own: workgroup
+// x = 0 writes it while the head's other workgroups run, so none of them may read it, nor a later one.
+constexpr int window_slot(int c, int u, int i) { return c + 16 * u < i ? c + 16 * u : -1; }
+constexpr bool window_slots_ok(int W) {
+  for (int i = 0; i < W; ++i) {
+    int n = 0;  // every earlier token has one lane
+    for (int u = 0; u < (W + 15) / 16; ++u)
+      for (int c = 0; c < 16; ++c) {
+        if (window_slot(c, u, i) >= i) return false;
+        n += window_slot(c, u, i) >= 0;
+      }
+    if (n != i) return false;
+  }
+  return true;
+}
+static_assert(window_slots_ok(8) && window_slots_ok(32), "a step reads the tokens before its own, each once");
+
 // The nonempty levels above `l0 - 1` (bit i of `rest`: level l0 + i), lowest first, KB at a time.
 template <int KB>
 struct LevelBatch {
@@ -211,16 +228,15 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
   };
   load_levels();
 
-  // this lane's tokens c, c + 16, .. of the window: v at the rows, requested with the levels (clamped
-  // to slots of the buffer; those at or past i are not used)
+  // this lane's tokens of the window: v at the rows, requested with the levels
   constexpr int WV = (W + 15) / 16;
   float vw[RB][WV];
 #pragma unroll
   for (int y = 0; y < RB; ++y)
 #pragma unroll
     for (int u = 0; u < WV; ++u) {
-      const int s = c + 16 * u < win.cap(L) ? c + 16 * u : win.cap(L) - 1;
-      vw[y][u] = to_f32(win.v[s * DV + row0 + 16 * y]);
+      const int s = window_slot(c, u, i);
+      vw[y][u] = s >= 0 ? to_f32(win.v[s * DV + row0 + 16 * y]) : 0.f;
     }
   float acc[RB];  // this thread's part of the rows' outputs
 #pragma unroll
@@ -297,7 +313,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
     if constexpr (!MERGE)
 #pragma unroll
       for (int u = 0; u < WV; ++u)
-        if (c + 16 * u < i) a += p_s[c + 16 * u] * vw[y][u];
+        if (const int s = window_slot(c, u, i); s >= 0) a += p_s[s] * vw[y][u];
     a = sum16(a);
     if (c == 0) o[bh * DV + row] = from_f32<T>(a + lam_of(0) * to_f32(v[bh * DV + row]) * kq);
   }
@@ -376,16 +392,15 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
   };
   load_levels();
 
-  // this lane's tokens c, c + 16, .. of the window: v at the rows, requested with the levels (clamped
-  // to slots of the buffer; those at or past i are not used)
+  // this lane's tokens of the window: v at the rows, requested with the levels
   constexpr int WV = (W + 15) / 16;
   float vw[RB][WV];
 #pragma unroll
   for (int y = 0; y < RB; ++y)
 #pragma unroll
     for (int u = 0; u < WV; ++u) {
-      const int s = c + 16 * u < win.cap(L) ? c + 16 * u : win.cap(L) - 1;
-      vw[y][u] = to_f32(win.v[s * DV + row0 + 16 * y]);
+      const int s = window_slot(c, u, i);
+      vw[y][u] = s >= 0 ? to_f32(win.v[s * DV + row0 + 16 * y]) : 0.f;
     }
   for (int e = tid; e < i * cap; e += kDecodeThreads) gr_s[e] = win.gram[e];  // its first i rows
   // wave 0: what the triangular solve needs besides, one token per lane
@@ -483,7 +498,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
     float a = acc[y];
 #pragma unroll
     for (int u = 0; u < WV; ++u)
-      if (c + 16 * u < i) a += p_s[c + 16 * u] * vw[y][u];
+      if (const int s = window_slot(c, u, i); s >= 0) a += p_s[s] * vw[y][u];
     a = sum16(a);
     if (c == 0) o[bh * DV + row] = from_f32<T>(a + p_s[i] * to_f32(v[bh * DV + row]));
   }
