@@ -105,11 +105,6 @@ struct RowPart {
   }
 };
 
-template <int DK>
-constexpr int kLogWindow = DK == 16 ? 3 : 5;
-template <int DK>
-constexpr int kLogWindowGdn = DK == 16 ? 3 : 5;
-
 // One head's window, in its level slots 0 .. min(LOGW, L - 1) (levels 0 .. LOGW are never stored as
 // matrices).  Two buffers alternate by window, so that the step that opens a window can store its
 // token while other workgroups still read the full one.  With L - 1 < LOGW levels the state holds
@@ -157,7 +152,7 @@ constexpr bool window_slots_ok(int W) {
   }
   return true;
 }
-static_assert(window_slots_ok(8) && window_slots_ok(32), "a step reads the tokens before its own, each once");
+static_assert(window_slots_ok(8) && window_slots_ok(16) && window_slots_ok(32), "a step reads the tokens before its own, each once");
 
 // The nonempty levels above `l0 - 1` (bit i of `rest`: level l0 + i), lowest first, KB at a time.
 template <int KB>
@@ -179,14 +174,14 @@ struct LevelBatch {
   }
 };
 
-template <typename T, int DK, int DV, int RB, bool MERGE>
+template <typename T, int DK, int DV, int LOGW, int RB, bool MERGE>
 __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const float* __restrict__ log_alpha,
     const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, const float* __restrict__ scale_in,
     float* __restrict__ scale_out, int64_t t, int L) {
   typedef RowPart<DK> RP;
-  typedef DecodeWindow<T, DK, DV, kLogWindow<DK>> Win;
-  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW;
+  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  constexpr int NPT = RP::NPT, W = Win::W;
   constexpr int KB = RB >= 4 ? 1 : 4;  // levels loaded together
   __shared__ float p_s[W];
   const int64_t bh = blockIdx.y;
@@ -348,14 +343,14 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
 // 70.5 (1024 heads, positions 3000 .. 3031).  Registers bound the waves in flight: the Gram rows in
 // registers instead of LDS, or spilling to 80 or 64 of them, cost 7 to 60 % of the step.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int DK, int DV, int RB>
+template <typename T, int DK, int DV, int LOGW, int RB>
 __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const float* __restrict__ log_alpha,
     const float* __restrict__ beta, const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, int64_t t,
     int L) {
   typedef RowPart<DK> RP;
-  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
-  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW;
+  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  constexpr int NPT = RP::NPT, W = Win::W;
   constexpr int KB = RB >= 4 ? 1 : 4;                 // levels loaded together
   constexpr int QP = kDecodeThreads / DK < W ? kDecodeThreads / DK : W;  // partial sums of q~ per column
   __shared__ __attribute__((aligned(16))) T k_s[W * DK];
@@ -516,14 +511,14 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
 // (16 lanes: 414 us for 6 levels of 1024 heads, d = 128; 8: 290).
 constexpr int kMergeLanes = 8;
 
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, int LOGW>
 __global__ __launch_bounds__(DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads) void
 k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                    const float* __restrict__ log_alpha, const float* __restrict__ beta, const float* __restrict__ lam,
                    T* __restrict__ o, float* __restrict__ S, int64_t t, int L) {
   typedef RowPart<DK, kMergeLanes> RP;
-  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
-  constexpr int NPT = RP::NPT, W = Win::W, LOGW = Win::LOGW, NB = 4;
+  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  constexpr int NPT = RP::NPT, W = Win::W, NB = 4;
   constexpr int NTH = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads, ROWS = NTH / kMergeLanes;
   __shared__ __attribute__((aligned(16))) float k_s[W * DK];
   __shared__ float bv_s[W * ROWS], b_s[W], al_s[W];
@@ -652,26 +647,51 @@ bool decode_wide(int64_t BH) {
   return DV % 64 == 0 && BH * (DV / 64) >= 1024;
 }
 
+// log2 of the window, the same for every step of a state (it depends on the state's sizes alone).  A longer window
+// merges less often and reads more rows meanwhile; a merge of W tokens is a chain as long as W that a small
+// batch waits for (its levels stay in the caches, where reading them costs little).  So 8 tokens below 2^21
+// matrix entries per level (BH d_k d_v), 32 where the levels come from memory, 16 between.  Mean of positions 2976 ..
+// 3039 and worst step, us, W = 8 / 16 / 32, d = 128: Mamba-2 4.7 / 4.7 / 5.1 and 7.9 / 8.8 / 10.2 (16 heads),
+// 18.0 / 17.6 / 18.7 and 28 / 31 / 37 (256), 75 / 67 / 62 and 113 / 105 / 132 (1024); Gated DeltaNet 6.3 / 6.3 / 7.0 and
+// 16 / 22 / 24, 22.3 / 21.8 / 24.0 and 43 / 53 / 61, 88 / 76 / 72 and 149 / 189 / 193.
+template <int DK, int DV>
+int decode_log_window(int64_t BH, bool gdn) {
+  if (DK == 16) return 3;  // a row is not much smaller than a matrix
+  const int64_t entries = BH * DK * DV;
+  return entries < (int64_t(1) << 21) ? 3 : entries < (int64_t(1) << (gdn ? 24 : 23)) ? 4 : 5;
+}
+// Calls f with the window's log2 as a compile-time constant.
+template <int DK, int DV, typename F>
+void with_log_window(int64_t BH, bool gdn, F f) {
+  const int log = decode_log_window<DK, DV>(BH, gdn);
+  if constexpr (DK != 16) {
+    if (log == 4) return f(std::integral_constant<int, 4>{});
+    if (log == 5) return f(std::integral_constant<int, 5>{});
+  }
+  f(std::integral_constant<int, 3>{});
+}
+
 template <typename T, int DK, int DV>
 hipError_t launch_decode(const void* q, const void* k, const void* v, const float* log_alpha, const float* lambda,
                          void* o, void* state, int64_t t, int64_t B, int64_t H, int L, hipStream_t st) {
-  typedef DecodeWindow<T, DK, DV, kLogWindow<DK>> Win;
   const DecodeLayout d = decode_layout(B, H, DK, DV, L);
   char* base = static_cast<char*>(state);
   const int64_t BH = B * H;
   float* S = reinterpret_cast<float*>(base + d.S);
   float* scale = reinterpret_cast<float*>(base + d.scale);
   const int par = (int)(t & 1);
-  const bool merge = t > 0 && t % Win::W == 0;
   constexpr int RW = DV % 64 == 0 ? 4 : 1;
   auto launch = [&](auto kernel, int rb) {
     hipLaunchKernelGGL(kernel, dim3(DV / (16 * rb), (unsigned)BH), dim3(kDecodeThreads), 0, st, (const T*)q,
                        (const T*)k, (const T*)v, log_alpha, lambda, (T*)o, S, scale + (1 - par) * BH * L,
                        scale + par * BH * L, t, L);
   };
-  if (merge) launch(k_decode_step<T, DK, DV, 1, true>, 1);
-  else if (decode_wide<DV>(BH)) launch(k_decode_step<T, DK, DV, RW, false>, RW);
-  else launch(k_decode_step<T, DK, DV, 1, false>, 1);
+  with_log_window<DK, DV>(BH, false, [&](auto log) {
+    constexpr int LOGW = decltype(log)::value;
+    if (t > 0 && t % (1 << LOGW) == 0) launch(k_decode_step<T, DK, DV, LOGW, 1, true>, 1);
+    else if (LOGW > 3 && decode_wide<DV>(BH)) launch(k_decode_step<T, DK, DV, LOGW, (LOGW > 3 ? RW : 1), false>, RW);
+    else launch(k_decode_step<T, DK, DV, LOGW, 1, false>, 1);
+  });
   return hipGetLastError();
 }
 
@@ -679,20 +699,22 @@ template <typename T, int DK, int DV>
 hipError_t launch_gdn_decode(const void* q, const void* k, const void* v, const float* log_alpha, const float* beta,
                              const float* lambda, void* o, void* state, int64_t t, int64_t B, int64_t H, int L,
                              hipStream_t st) {
-  typedef DecodeWindow<T, DK, DV, kLogWindowGdn<DK>> Win;
   const DecodeLayout d = decode_layout(B, H, DK, DV, L);
   const int64_t BH = B * H;
   float* S = reinterpret_cast<float*>(static_cast<char*>(state) + d.S);
-  const bool merge = t > 0 && t % Win::W == 0;
   constexpr int RW = DV % 64 == 0 ? 4 : 1;
   auto launch = [&](auto kernel, int threads, int rows) {  // rows of d_v per workgroup
     hipLaunchKernelGGL(kernel, dim3(DV / rows, (unsigned)BH), dim3(threads), 0, st, (const T*)q, (const T*)k,
                        (const T*)v, log_alpha, beta, lambda, (T*)o, S, t, L);
   };
   constexpr int MT = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads;
-  if (merge) launch(k_gdn_decode_merge<T, DK, DV>, MT, MT / kMergeLanes);
-  else if (decode_wide<DV>(BH)) launch(k_gdn_decode_step<T, DK, DV, RW>, kDecodeThreads, 16 * RW);
-  else launch(k_gdn_decode_step<T, DK, DV, 1>, kDecodeThreads, 16);
+  with_log_window<DK, DV>(BH, true, [&](auto log) {
+    constexpr int LOGW = decltype(log)::value;
+    if (t > 0 && t % (1 << LOGW) == 0) launch(k_gdn_decode_merge<T, DK, DV, LOGW>, MT, MT / kMergeLanes);
+    else if (LOGW > 3 && decode_wide<DV>(BH))
+      launch(k_gdn_decode_step<T, DK, DV, LOGW, (LOGW > 3 ? RW : 1)>, kDecodeThreads, 16 * RW);
+    else launch(k_gdn_decode_step<T, DK, DV, LOGW, 1>, kDecodeThreads, 16);
+  });
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""Decoding at the edges of the token window (the tokens since the last multiple of W = 32, or 8 for
-d = 16, are kept as rows; the step that opens a window merges the last one): states of few levels,
+"""Decoding at the edges of the token window (the tokens since the last multiple of W = 8, 16 or 32, by the batch's
+size, are kept as rows; the step that opens a window merges the last one): states of few levels,
 whose window is shorter than W, sequences around one and several merges, a gate that resets the
 state, decays under which levels vanish, the kernels with 64 rows of d_v per workgroup (large batches)
 and a state copied in the middle of a window.  References and bars are those of test_gpu_decode.py and test_gpu_gdn_decode.py:
@@ -134,3 +134,22 @@ def test_decayed_levels(dtype, d, rep):
     for h in range(3):
         assert rel_err(got[:, h, 0], ref[:, h]) <= TOL[dtype], h
     assert (got == got[:, :, :1]).all()
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+@pytest.mark.parametrize("dtype,d,rep", [
+    ("bf16", (128, 128), 42),   # 126 heads: windows of 8 tokens, the most heads that have them
+    ("bf16", (128, 128), 43),   # 129 heads: 16 tokens
+    ("bf16", (128, 64), 100),   # 300 heads: 16
+    ("f32", (64, 64), 200),     # 600 heads: 16, 16 rows of d_v per workgroup
+    ("f32", (64, 64), 700),     # 2100 heads: 32 (Gated DeltaNet 16), 64 rows
+    ("bf16", (64, 64), 1400),   # 4200 heads: 32
+    ("bf16", (128, 128), 350),  # 1050 heads: 32
+])
+def test_window_lengths(variant, dtype, d, rep):
+    """Every length of the window at its edges: a state too short for one, the first merges, some more tokens."""
+    for T in (2, 17, 33, 100):
+        x = inputs(variant, dtype, d, T)
+        got = Decoder(variant, x, dtype, fenwick.num_levels(T), rep).feed(0, T).reshape(T, 3, rep, d[1])
+        assert (got == got[:, :, :1]).all(), T
+        assert rel_err(got[:, :, 0], reference(variant, x)) <= TOL[dtype], T
