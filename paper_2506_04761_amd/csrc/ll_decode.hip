@@ -11,7 +11,7 @@
 //   S      [B*H][L][d_v][d_k] fp32   levels LOGW + 1 .. L-1, each kept as c_l * S_stored; the slots
 //                                    below them hold the head's window (DecodeWindow)
 //   scale  [2][B*H][L]        fp32   c_l, double-buffered by step parity (read t-1, write t)
-//   f0     [2][B*H][d_v + d_k] fp32  unused (the buffer's size is part of the interface)
+//   f0     [2][B*H][d_v + d_k] fp32  level 0 in factored form (k_gdn_decode_plain)
 //
 // Window.  The tokens since the last multiple of W = 2^LOGW are kept as their rows of k and v, not
 // as matrices: within one aligned window no level above LOGW changes but for its decay, and the
@@ -22,10 +22,9 @@
 // at most W rows, and writes a matrix once in W steps; kept as matrices, levels 1 .. LOGW cost half
 // of LOGW more level reads and one level write at every step.  The decays are applied lazily, through
 // one fp32 scale per level and one per window token (double-buffered by step parity like the scales).
-// W = 32 (8 for d = 16, where a row is not much smaller than a matrix).  Bound: reading the levels.  1024
-// heads, d = 128, bf16, positions 3000 .. 3031: 111 -> 64 us a step, 5 levels (335 MB) at 5.2 TB/s
-// against 8 read and one written; 54 us with the levels that have decayed to nothing left out.  W = 16, 32, 64 at positions 1984 .. 2111: 51.8, 50.0, 49.5 us
-// (1024 heads), 17.4, 18.5, 20.5 us (256 heads).
+// W = 8, 16 or 32 by the batch's size (decode_log_window).  Bound: reading the levels.  1024 heads, d = 128,
+// bf16, W = 32, positions 3000 .. 3031: 111 -> 64 us a step, 5 levels (335 MB) at 5.2 TB/s against 8 read and
+// one written; 54 us with the levels that have decayed to nothing left out.
 //
 // Work split: grid (d_v / (16 RB), B*H), 256 threads; thread (row r = tid / 16, part c = tid % 16)
 // owns d_v rows 16 (RB blockIdx.x + i) + r, i < RB, and 16-byte pieces c, c + 16, .. of every d_k
@@ -291,9 +290,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
 #pragma unroll
     for (int b = 0; b < KB; ++b)
       if (b < lv.n) {
-        const float cl = cin[lv.l[b]];
-        if (cl == 0.f) continue;
-        const float w = lam_of(lv.l[b]) * cl * alpha;
+        const float w = lam_of(lv.l[b]) * cin[lv.l[b]] * alpha;
 #pragma unroll
         for (int y = 0; y < RB; ++y) acc[y] += w * RP::dot(x[b][y], qv);
       }
@@ -632,6 +629,81 @@ k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __
   }
 }
 
+// Every level kept as a matrix, its transition applied at each token: small batches, whose levels stay in the
+// caches.  Level 0 is kept in factored form, f0: beta v and k of the previous token.  Row x of a level takes
+// x <- alpha (x - beta (x . k) k) on its own, the split is that of k_gdn_decode_step, and for t >= 1, with
+// p = lssb(t), level p + 1 is first the sum of levels 0 .. p.
+template <typename T, int DK, int DV>
+__global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_plain(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const float* __restrict__ log_alpha,
+    const float* __restrict__ beta, const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S,
+    const float* __restrict__ f0_in, float* __restrict__ f0_out, int64_t t, int L) {
+  typedef RowPart<DK> RP;
+  constexpr int NPT = RP::NPT, NB = 4;  // levels loaded together
+  const int64_t bh = blockIdx.y;
+  const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
+  const int row = blockIdx.x * 16 + r;
+  float* Sh = S + bh * (int64_t)L * DV * DK;
+  auto lam_of = [&](int l) { return lam ? lam[bh * L + l] : 1.f; };
+  auto level_row = [&](int l) { return Sh + ((int64_t)l * DV + row) * DK; };
+  float x[NB][NPT];
+  LevelBatch<NB> lv;
+  int64_t rest = 0;
+  int l0 = 0;
+  auto load_levels = [&]() {
+    lv.next(rest, l0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < lv.n) RP::load(level_row(lv.l[b]), c, x[b]);
+  };
+
+  float qv[NPT], kv[NPT];
+  RP::load(q + bh * DK, c, qv);
+  RP::load(k + bh * DK, c, kv);
+  const float alpha = expf(log_alpha[bh]), bt = beta[bh];
+  const float kq = sum16(RP::dot(kv, qv));
+  float acc = 0.f;  // the row's output (the same in its 16 lanes)
+  auto step_level = [&](float (&y)[NPT], int l) {
+    const float a = sum16(RP::dot(y, kv)), b = sum16(RP::dot(y, qv));
+#pragma unroll
+    for (int e = 0; e < NPT; ++e) y[e] = alpha * (y[e] - bt * a * kv[e]);
+    RP::store(level_row(l), c, y);
+    acc += lam_of(l) * alpha * (b - bt * kq * a);
+  };
+  if (t > 0) {
+    const int p = __builtin_ctzll((unsigned long long)t);
+    const float* f = f0_in + bh * (DV + DK);
+    const float bv = f[row];
+    float m[NPT];
+    RP::load(f + DV, c, m);
+#pragma unroll
+    for (int e = 0; e < NPT; ++e) m[e] *= bv;
+    rest = (int64_t(1) << p) - 1;  // levels 1 .. p
+    l0 = 1;
+    for (load_levels(); lv.n; load_levels())
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (b < lv.n)
+#pragma unroll
+          for (int e = 0; e < NPT; ++e) m[e] += x[b][e];
+    rest = t >> (p + 1);  // the others that hold tokens
+    l0 = p + 2;
+    load_levels();
+    step_level(m, p + 1);
+    for (; lv.n; load_levels())
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (b < lv.n) step_level(x[b], lv.l[b]);
+  }
+  if (c == 0) o[bh * DV + row] = from_f32<T>(acc + lam_of(0) * bt * to_f32(v[bh * DV + row]) * kq);
+
+  if (blockIdx.x == 0) {
+    float* f = f0_out + bh * (DV + DK);
+    for (int e = tid; e < DV; e += kDecodeThreads) f[e] = bt * to_f32(v[bh * DV + e]);
+    for (int e = tid; e < DK; e += kDecodeThreads) f[DV + e] = to_f32(k[bh * DK + e]);
+  }
+}
+
 // Zero-fills n floats (the decode state before its first token).
 __global__ void k_zero_f32(float* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -652,18 +724,23 @@ bool decode_wide(int64_t BH) {
 // batch waits for (its levels stay in the caches, where reading them costs little).  So 8 tokens below 2^21
 // matrix entries per level (BH d_k d_v), 32 where the levels come from memory, 16 between.  Mean of positions 2976 ..
 // 3039 and worst step, us, W = 8 / 16 / 32, d = 128: Mamba-2 4.7 / 4.7 / 5.1 and 7.9 / 8.8 / 10.2 (16 heads),
-// 18.0 / 17.6 / 18.7 and 28 / 31 / 37 (256), 75 / 67 / 62 and 113 / 105 / 132 (1024); Gated DeltaNet 6.3 / 6.3 / 7.0 and
-// 16 / 22 / 24, 22.3 / 21.8 / 24.0 and 43 / 53 / 61, 88 / 76 / 72 and 149 / 189 / 193.
+// 18.0 / 17.6 / 18.7 and 28 / 31 / 37 (256), 75 / 67 / 62 and 113 / 105 / 132 (1024); Gated DeltaNet 7.8 / 7.6 / 8.7 and
+// 20 / 25 / 28 (64), 22.3 / 21.8 / 24.0 and 43 / 53 / 61 (256), 88 / 76 / 72 and 149 / 189 / 193 (1024).  0: Gated DeltaNet
+// without a window (k_gdn_decode_plain) up to 2^19 entries (2^18 for d = 16); without and with W = 8, positions 0 .. 31,
+// 96 .. 159, 2976 .. 3039 and the last's worst step, d = 128: 4.0, 4.4, 5.7, 9.0 us and 4.8, 5.3, 6.3, 16 (16 heads);
+// 5.2, 6.5, 10.1, 15.6 and 5.4, 6.2, 7.9, 19.4 (64 heads); 128 x 64: 4.5, 5.3, 6.9, 10.7 and 5.0, 5.6, 6.9, 19.2 (64 heads).
 template <int DK, int DV>
 int decode_log_window(int64_t BH, bool gdn) {
-  if (DK == 16) return 3;  // a row is not much smaller than a matrix
   const int64_t entries = BH * DK * DV;
+  if (gdn && entries <= (int64_t(1) << (DK == 16 ? 18 : 19))) return 0;
+  if (DK == 16) return 3;  // a row is not much smaller than a matrix
   return entries < (int64_t(1) << 21) ? 3 : entries < (int64_t(1) << (gdn ? 24 : 23)) ? 4 : 5;
 }
 // Calls f with the window's log2 as a compile-time constant.
 template <int DK, int DV, typename F>
 void with_log_window(int64_t BH, bool gdn, F f) {
   const int log = decode_log_window<DK, DV>(BH, gdn);
+  if (log == 0) return f(std::integral_constant<int, 0>{});
   if constexpr (DK != 16) {
     if (log == 4) return f(std::integral_constant<int, 4>{});
     if (log == 5) return f(std::integral_constant<int, 5>{});
@@ -687,7 +764,7 @@ hipError_t launch_decode(const void* q, const void* k, const void* v, const floa
                        scale + par * BH * L, t, L);
   };
   with_log_window<DK, DV>(BH, false, [&](auto log) {
-    constexpr int LOGW = decltype(log)::value;
+    constexpr int LOGW = decltype(log)::value > 3 ? decltype(log)::value : 3;
     if (t > 0 && t % (1 << LOGW) == 0) launch(k_decode_step<T, DK, DV, LOGW, 1, true>, 1);
     else if (LOGW > 3 && decode_wide<DV>(BH)) launch(k_decode_step<T, DK, DV, LOGW, (LOGW > 3 ? RW : 1), false>, RW);
     else launch(k_decode_step<T, DK, DV, LOGW, 1, false>, 1);
@@ -710,10 +787,19 @@ hipError_t launch_gdn_decode(const void* q, const void* k, const void* v, const 
   constexpr int MT = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads;
   with_log_window<DK, DV>(BH, true, [&](auto log) {
     constexpr int LOGW = decltype(log)::value;
-    if (t > 0 && t % (1 << LOGW) == 0) launch(k_gdn_decode_merge<T, DK, DV, LOGW>, MT, MT / kMergeLanes);
-    else if (LOGW > 3 && decode_wide<DV>(BH))
+    if constexpr (LOGW == 0) {
+      float* f0 = reinterpret_cast<float*>(static_cast<char*>(state) + d.f0);
+      const int64_t par = t & 1, n = BH * (DV + DK);
+      hipLaunchKernelGGL((k_gdn_decode_plain<T, DK, DV>), dim3(DV / 16, (unsigned)BH), dim3(kDecodeThreads), 0, st,
+                         (const T*)q, (const T*)k, (const T*)v, log_alpha, beta, lambda, (T*)o, S, f0 + (1 - par) * n,
+                         f0 + par * n, t, L);
+    } else if (t > 0 && t % (1 << LOGW) == 0) {
+      launch(k_gdn_decode_merge<T, DK, DV, LOGW>, MT, MT / kMergeLanes);
+    } else if (LOGW > 3 && decode_wide<DV>(BH)) {
       launch(k_gdn_decode_step<T, DK, DV, LOGW, (LOGW > 3 ? RW : 1)>, kDecodeThreads, 16 * RW);
-    else launch(k_gdn_decode_step<T, DK, DV, LOGW, 1>, kDecodeThreads, 16);
+    } else {
+      launch(k_gdn_decode_step<T, DK, DV, LOGW, 1>, kDecodeThreads, 16);
+    }
   });
   return hipGetLastError();
 }

@@ -108,16 +108,17 @@ def test_large_batch(variant, d):
     assert rel_err(got[:, :, 0], reference(variant, x)) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("rep", [1, 11])
 @pytest.mark.parametrize("variant", ["mamba2", "gdn"])
-def test_copied_state(variant):
+def test_copied_state(variant, rep):
     """A state copied in the middle of a window continues like the original, and the original is not
     touched by the copy's steps."""
     x = inputs(variant, "bf16", (128, 128), 110)
-    dec = Decoder(variant, x, "bf16", fenwick.num_levels(110))
+    dec = Decoder(variant, x, "bf16", fenwick.num_levels(110), rep)
     dec.feed(0, 77)
     fork = dec.state.clone()
     a, b = dec.feed(77, 110, fork), dec.feed(77, 110)
-    assert (a == b).all() and rel_err(b, reference(variant, x)[77:]) <= TOL["bf16"]
+    assert (a == b).all() and rel_err(b[:, ::rep], reference(variant, x)[77:]) <= TOL["bf16"]
 
 
 @pytest.mark.parametrize("dtype,d,rep", [("f32", (16, 16), 1), ("bf16", (128, 128), 1), ("bf16", (128, 128), 400)])
@@ -138,7 +139,10 @@ def test_decayed_levels(dtype, d, rep):
 
 @pytest.mark.parametrize("variant", ["mamba2", "gdn"])
 @pytest.mark.parametrize("dtype,d,rep", [
-    ("bf16", (128, 128), 42),   # 126 heads: windows of 8 tokens, the most heads that have them
+    ("bf16", (64, 64), 42),     # 126 heads: Gated DeltaNet keeps every level as a matrix
+    ("bf16", (64, 64), 43),     # 129 heads: windows of 8 tokens
+    ("f32", (16, 16), 342),     # 1026 heads: 8
+    ("bf16", (128, 128), 42),   # 126 heads: 8, the most of this size
     ("bf16", (128, 128), 43),   # 129 heads: 16 tokens
     ("bf16", (128, 64), 100),   # 300 heads: 16
     ("f32", (64, 64), 200),     # 600 heads: 16, 16 rows of d_v per workgroup
