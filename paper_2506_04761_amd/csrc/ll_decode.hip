@@ -104,6 +104,11 @@ struct RowPart {
   }
 };
 
+// Storage of a window's rows: that of k and v, but fp32 for the shape compiled for both types, so that steps of
+// either type may follow each other on one state (bf16 values are exact in it).
+template <typename T, int DK, int DV>
+using WindowRow = std::conditional_t<DK == 64 && DV == 64, float, T>;
+
 // One head's window, in its level slots 0 .. min(LOGW, L - 1) (levels 0 .. LOGW are never stored as
 // matrices).  Two buffers alternate by window, so that the step that opens a window can store its
 // token while other workgroups still read the full one.  With L - 1 < LOGW levels the state holds
@@ -179,7 +184,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
     const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, const float* __restrict__ scale_in,
     float* __restrict__ scale_out, int64_t t, int L) {
   typedef RowPart<DK> RP;
-  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  typedef WindowRow<T, DK, DV> Row;
+  typedef DecodeWindow<Row, DK, DV, LOGW> Win;
   constexpr int NPT = RP::NPT, W = Win::W;
   constexpr int KB = RB >= 4 ? 1 : 4;  // levels loaded together
   __shared__ float p_s[W];
@@ -318,8 +324,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
       const bool held = l > LOGW && ((t >> (l - 1)) & 1);
       cout[l] = !held ? 0.f : (MERGE && l == p + 1) ? alpha : cin[l] * alpha;
     }
-    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = k[bh * DK + e];
-    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = v[bh * DV + e];
+    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = from_f32<Row>(to_f32(k[bh * DK + e]));
+    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = from_f32<Row>(to_f32(v[bh * DV + e]));
     if (tid == 0) dec_out[i] = 1.f;
   }
 }
@@ -346,11 +352,12 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
     const float* __restrict__ beta, const float* __restrict__ lam, T* __restrict__ o, float* __restrict__ S, int64_t t,
     int L) {
   typedef RowPart<DK> RP;
-  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  typedef WindowRow<T, DK, DV> Row;
+  typedef DecodeWindow<Row, DK, DV, LOGW> Win;
   constexpr int NPT = RP::NPT, W = Win::W;
   constexpr int KB = RB >= 4 ? 1 : 4;                 // levels loaded together
   constexpr int QP = kDecodeThreads / DK < W ? kDecodeThreads / DK : W;  // partial sums of q~ per column
-  __shared__ __attribute__((aligned(16))) T k_s[W * DK];
+  __shared__ __attribute__((aligned(16))) Row k_s[W * DK];
   __shared__ __attribute__((aligned(16))) float qp_s[QP * DK];
   __shared__ float a_s[W], g_s[W], cf_s[W], p_s[W], gr_s[W * W + 64], db_s;  // gr_s: 64 lanes read a row
   const int64_t bh = blockIdx.y;
@@ -495,8 +502,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
     if (c == 0) o[bh * DV + row] = from_f32<T>(a + p_s[i] * to_f32(v[bh * DV + row]));
   }
   if (blockIdx.x == 0) {
-    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = k[bh * DK + e];
-    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = v[bh * DV + e];
+    for (int e = tid; e < DK; e += kDecodeThreads) win.k[i * DK + e] = from_f32<Row>(to_f32(k[bh * DK + e]));
+    for (int e = tid; e < DV; e += kDecodeThreads) win.v[i * DV + e] = from_f32<Row>(to_f32(v[bh * DV + e]));
   }
 }
 
@@ -514,7 +521,8 @@ k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __
                    const float* __restrict__ log_alpha, const float* __restrict__ beta, const float* __restrict__ lam,
                    T* __restrict__ o, float* __restrict__ S, int64_t t, int L) {
   typedef RowPart<DK, kMergeLanes> RP;
-  typedef DecodeWindow<T, DK, DV, LOGW> Win;
+  typedef WindowRow<T, DK, DV> Row;
+  typedef DecodeWindow<Row, DK, DV, LOGW> Win;
   constexpr int NPT = RP::NPT, W = Win::W, NB = 4;
   constexpr int NTH = DV * kMergeLanes < kDecodeThreads ? DV * kMergeLanes : kDecodeThreads, ROWS = NTH / kMergeLanes;
   __shared__ __attribute__((aligned(16))) float k_s[W * DK];
@@ -617,8 +625,8 @@ k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __
   if (c == 0) o[bh * DV + row] = from_f32<T>(acc + lam_of(0) * bt * to_f32(v[bh * DV + row]) * kq);
 
   if (blockIdx.x == 0) {
-    for (int e = tid; e < DK; e += NTH) win.k[e] = k[bh * DK + e];
-    for (int e = tid; e < DV; e += NTH) win.v[e] = v[bh * DV + e];
+    for (int e = tid; e < DK; e += NTH) win.k[e] = from_f32<Row>(to_f32(k[bh * DK + e]));
+    for (int e = tid; e < DV; e += NTH) win.v[e] = from_f32<Row>(to_f32(v[bh * DV + e]));
     if (tid == 0) {
       win.beta[0] = bt;
       win.alpha[0] = alpha;

@@ -157,3 +157,23 @@ def test_window_lengths(variant, dtype, d, rep):
         got = Decoder(variant, x, dtype, fenwick.num_levels(T), rep).feed(0, T).reshape(T, 3, rep, d[1])
         assert (got == got[:, :, :1]).all(), T
         assert rel_err(got[:, :, 0], reference(variant, x)) <= TOL[dtype], T
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+@pytest.mark.parametrize("rep", [1, 43, 200, 1400])  # every length of the window (Gated DeltaNet: and none)
+def test_steps_of_both_types_on_one_state(variant, rep):
+    """d = 64 is compiled for fp32 and bf16, and a state belongs to neither: steps of the two types in turn, with
+    values that both hold exactly, give the sequence's rows, each within the bar of its output's type."""
+    T = 100
+    x = inputs(variant, "bf16", (64, 64), T)
+    ref = reference(variant, x)
+    dec = {dt: Decoder(variant, x, dt, fenwick.num_levels(T), rep) for dt in ("f32", "bf16")}
+    order = ["f32" if t % 3 == 0 or 60 < t < 80 else "bf16" for t in range(T)]
+    got = np.concatenate([dec[dt].feed(t, t + 1, dec["bf16"].state) for t, dt in enumerate(order)])
+    got = got.reshape(T, 3, rep, 64)
+    assert (got == got[:, :, :1]).all()
+    for dt in ("f32", "bf16"):
+        rows = [t for t in range(T) if order[t] == dt]
+        err = rel_err(got[rows, :, 0], ref[rows])
+        print(f"{variant} {dt} rows of a mixed sequence, {3 * rep} heads: {err:.2e}", flush=True)
+        assert err <= TOL[dt]
