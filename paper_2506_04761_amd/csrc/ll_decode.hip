@@ -189,6 +189,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
   constexpr int NPT = RP::NPT, W = Win::W;
   constexpr int KB = RB >= 4 ? 1 : 4;  // levels loaded together
   __shared__ float p_s[W];
+  constexpr float kLeftOut = -0.f;  // (x + 0 is never -0)
   const int64_t bh = blockIdx.y;
   const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
   const int row0 = blockIdx.x * 16 * RB + r;  // rows row0 + 16 x
@@ -216,6 +217,13 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
   const int lane = tid & 63;
   const float cl_lane = cin[lane < L ? lane : 0];
   rest &= (int64_t)(__ballot(lane < L && cl_lane != 0.f) >> l0);
+  // Tokens decayed to nothing are left out like such levels, whatever they hold (0 times a value that is not finite
+  // would stay): of the window merged below, those before s0 (the decays do not fall from token to token).
+  int s0 = 0;
+  if constexpr (MERGE) {
+    const uint64_t live = __ballot(lane < W && dec_in[lane < W ? lane : 0] != 0.f);
+    s0 = live ? __builtin_ctzll(live) : W;
+  }
   LevelBatch<KB> lv;
   float x[KB][RB][NPT];
   auto load_levels = [&]() {
@@ -249,8 +257,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
     for (int y = 0; y < RB; ++y)
 #pragma unroll
       for (int e = 0; e < NPT; ++e) m[y][e] = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < W; ++s) {
+    auto add_token = [&](int s) {
       const float d = dec_in[s];
       float ks[NPT];
       RP::load(full.k + s * DK, c, ks);
@@ -260,6 +267,12 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
 #pragma unroll
         for (int e = 0; e < NPT; ++e) m[y][e] += vs * ks[e];
       }
+    };
+    if (s0 == 0) {
+#pragma unroll 4
+      for (int s = 0; s < W; ++s) add_token(s);
+    } else {
+      for (int s = s0; s < W; ++s) add_token(s);
     }
     for (int l = LOGW + 1; l <= p; ++l) {
       const float cl = cin[l];
@@ -285,8 +298,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
       RP::load(win.k + s * DK, c, ks);
       const float a = sum16(RP::dot(ks, qv));
       if (c == 0) {
-        const float d = dec_in[s] * alpha;
-        p_s[s] = lam_of(bitlen(uint32_t(i ^ s))) * d * a;
+        const float d0 = dec_in[s], d = d0 * alpha, w = lam_of(bitlen(uint32_t(i ^ s))) * d * a + 0.f;
+        p_s[s] = d0 != 0.f ? w : kLeftOut;
         if (blockIdx.x == 0) dec_out[s] = d;
       }
     }
@@ -304,14 +317,23 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
   }
   // the token itself, level 0: v_t[row] (k_t . q_t)
   const float kq = sum16(RP::dot(kv, qv));
+  float pw[WV];
+  if constexpr (!MERGE)
+#pragma unroll
+    for (int u = 0; u < WV; ++u) {
+      const int s = window_slot(c, u, i);
+      pw[u] = s >= 0 ? p_s[s] : kLeftOut;
+      const bool out = __float_as_uint(pw[u]) == __float_as_uint(kLeftOut);
+#pragma unroll
+      for (int y = 0; y < RB; ++y) vw[y][u] = out ? 0.f : vw[y][u];
+    }
 #pragma unroll
   for (int y = 0; y < RB; ++y) {
     const int row = row0 + 16 * y;
     float a = acc[y];
     if constexpr (!MERGE)
 #pragma unroll
-      for (int u = 0; u < WV; ++u)
-        if (const int s = window_slot(c, u, i); s >= 0) a += p_s[s] * vw[y][u];
+      for (int u = 0; u < WV; ++u) a += pw[u] * vw[y][u];
     a = sum16(a);
     if (c == 0) o[bh * DV + row] = from_f32<T>(a + lam_of(0) * to_f32(v[bh * DV + row]) * kq);
   }

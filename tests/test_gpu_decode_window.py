@@ -177,3 +177,20 @@ def test_steps_of_both_types_on_one_state(variant, rep):
         err = rel_err(got[rows, :, 0], ref[rows])
         print(f"{variant} {dt} rows of a mixed sequence, {3 * rep} heads: {err:.2e}", flush=True)
         assert err <= TOL[dt]
+
+
+@pytest.mark.parametrize("at,reset", [(3, 5), (10, 20), (10, 33), (31, 32), (31, 64), (40, 70)])
+@pytest.mark.parametrize("name", ["k", "v"])
+@pytest.mark.parametrize("rep", [1, 200, 700])  # every length of the window
+def test_reset_drops_what_is_not_finite(at, reset, name, rep):
+    """Mamba-2: after alpha = 0 the levels and the tokens before it are not read, so an infinity or a NaN among
+    them ends there: the rows after the reset are those of the sequence without it."""
+    T = 100
+    x = inputs("mamba2", "f32", (64, 64), T)
+    x["log_alpha"][:, reset] = -np.inf
+    ref = reference("mamba2", x)
+    x[name][0, at, 0, 5], x[name][0, at, 1, 7] = np.inf, np.nan
+    got = Decoder("mamba2", x, "f32", fenwick.num_levels(T), rep).feed(0, T).reshape(T, 3, rep, 64)[:, :, 0]
+    assert not np.isfinite(got[at, 0]).all() and not np.isfinite(got[at, 1]).all()
+    assert np.isfinite(got[reset + 1:]).all()
+    assert rel_err(got[reset + 1:], ref[reset + 1:]) <= TOL["f32"] and rel_err(got[:, 2], ref[:, 2]) <= TOL["f32"]
