@@ -75,9 +75,10 @@ template <int DK, int LANES = 16>
 struct RowPart {
   static constexpr int NPT = DK / LANES, VEC = NPT < 4 ? NPT : 4, PIECES = NPT / VEC;
   static_assert(LANES * VEC * PIECES == DK, "whole pieces");
-  template <typename T>
+  // ALIGN: of the rows; a caller's q and k may begin at any element
+  template <int ALIGN = 0, typename T>
   __device__ static void load(const T* row, int c, float (&x)[NPT]) {
-    typedef T vec __attribute__((ext_vector_type(VEC)));
+    typedef T vec __attribute__((ext_vector_type(VEC), aligned(ALIGN ? ALIGN : VEC * sizeof(T))));
 #pragma unroll
     for (int j = 0; j < PIECES; ++j) {
       const vec y = *reinterpret_cast<const vec*>(row + LANES * VEC * j + VEC * c);
@@ -203,8 +204,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
   auto level_row = [&](int l, int x) { return Sh + ((int64_t)l * DV + row0 + 16 * x) * DK; };
 
   float qv[NPT], kv[NPT];
-  RP::load(q + bh * DK, c, qv);
-  RP::load(k + bh * DK, c, kv);
+  RP::template load<sizeof(T)>(q + bh * DK, c, qv);
+  RP::template load<sizeof(T)>(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]);
 
   // levels that carry over, decayed by alpha_t; the first batch's rows are requested before the window
@@ -395,8 +396,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
   auto level_row = [&](int l, int x) { return Sh + ((int64_t)l * DV + row0 + 16 * x) * DK; };
 
   float qv[NPT], kv[NPT];
-  RP::load(q + bh * DK, c, qv);
-  RP::load(k + bh * DK, c, kv);
+  RP::template load<sizeof(T)>(q + bh * DK, c, qv);
+  RP::template load<sizeof(T)>(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]), bt = beta[bh];
 
   int64_t rest = t >> LOGW;
@@ -570,8 +571,8 @@ k_gdn_decode_merge(const T* __restrict__ q, const T* __restrict__ k, const T* __
     al_s[s] = full.alpha[s];
   }
   float qt[NPT], kv[NPT];  // q~ = alpha_t (q - beta_t (k . q) k)
-  RP::load(q + bh * DK, c, qt);
-  RP::load(k + bh * DK, c, kv);
+  RP::template load<sizeof(T)>(q + bh * DK, c, qt);
+  RP::template load<sizeof(T)>(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]), bt = beta[bh];
   const float kq = sum8(RP::dot(kv, qt));
 #pragma unroll
@@ -688,8 +689,8 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_plain(
   };
 
   float qv[NPT], kv[NPT];
-  RP::load(q + bh * DK, c, qv);
-  RP::load(k + bh * DK, c, kv);
+  RP::template load<sizeof(T)>(q + bh * DK, c, qv);
+  RP::template load<sizeof(T)>(k + bh * DK, c, kv);
   const float alpha = expf(log_alpha[bh]), bt = beta[bh];
   const float kq = sum16(RP::dot(kv, qv));
   float acc = 0.f;  // the row's output (the same in its 16 lanes)

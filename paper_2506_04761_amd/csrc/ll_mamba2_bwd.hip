@@ -1379,11 +1379,12 @@ __global__ __launch_bounds__(kBwdFastThreads, 2) void k_bwd_dkv_fast(
     if (tid == R - 1) tsum[bh * N + u] = x;
   }
   if (!GROUP || (!dk32 && hx == HN - 1)) {
+  typedef bf16x8 dk_vec __attribute__((aligned(2)));  // the caller's dk may begin at any element (see k_group_sum)
 #pragma unroll
   for (int it = 0; it < R * (DK / 8) / NT; ++it) {
     const int idx = it * NT + tid, r = idx / (DK / 8), c = idx % (DK / 8);
     if (r < nrow)
-      *reinterpret_cast<bf16x8*>(dk + ((row0 + r) * HP + hp) * DK + 8 * c) =
+      *reinterpret_cast<dk_vec*>(dk + ((row0 + r) * HP + hp) * DK + 8 * c) =
           *reinterpret_cast<const bf16x8*>(q_s + swz<DK>(r, c));
   }
   }
@@ -1493,7 +1494,8 @@ __global__ __launch_bounds__(256) void k_group_sum(const Tin* __restrict__ in, T
   vec res;
 #pragma unroll
   for (int e = 0; e < V; ++e) res[e] = from_f32<T>(acc[e]);
-  *reinterpret_cast<vec*>(out + idx * V) = res;
+  typedef T vec_any __attribute__((ext_vector_type(V), aligned(sizeof(T))));  // dq, dk may begin at any element
+  *reinterpret_cast<vec_any*>(out + idx * V) = res;
 }
 
 int64_t mamba2_bwd_workspace(int64_t B, int64_t T, int64_t H, int64_t Hqk, int64_t dk, int64_t dv, int64_t C,

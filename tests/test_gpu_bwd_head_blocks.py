@@ -119,3 +119,23 @@ def test_dk_is_no_further_from_float64_than_a_sum_of_rounded_heads(B, H, Hqk, T,
     err = lambda x: float((x - exact).norm() / exact.norm())
     print(f"dk: {err(got):.3e}, heads rounded one by one {err(per_head):.3e}", flush=True)
     assert err(got) < 0.95 * err(per_head)
+
+
+@pytest.mark.parametrize("Hqk", [1, 16, 32])  # dq and dk from k_group_sum; dk from blocks of 2 heads; the same, nothing to sum
+def test_shared_gradients_begin_at_any_element(Hqk):
+    """dq and dk of shared heads one element past an aligned address: the same bits as at an aligned one."""
+    import torch
+    import paper_2506_04761_amd as ll
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B, H, T, dk, dv = 2, 64, 1984, 128, 64
+    g = torch.Generator(device="cuda").manual_seed(Hqk)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k = ((rnd(B, T, Hqk, dk) / dk ** 0.5).bfloat16() for _ in range(2))
+    v, do = (rnd(B, T, H, dv) / dv ** 0.5).bfloat16(), rnd(B, T, H, dv).bfloat16()
+    la = -torch.nn.functional.softplus(rnd(B, T, H) - 3)
+    lam = torch.nn.functional.softplus(rnd(B, T, H, ll.ll_num_levels(T)))
+    ref = ll.ll_mamba2_bwd(q, k, v, la, lam, do, 64)
+    dq, dkk = (torch.zeros(q.numel() + 1, dtype=q.dtype, device="cuda")[1:].view(q.shape) for _ in range(2))
+    got = ll.ll_mamba2_bwd(q, k, v, la, lam, do, 64, grads=(dq, dkk, *(torch.empty_like(r) for r in ref[2:])))
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))

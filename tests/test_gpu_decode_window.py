@@ -194,3 +194,17 @@ def test_reset_drops_what_is_not_finite(at, reset, name, rep):
     assert not np.isfinite(got[at, 0]).all() and not np.isfinite(got[at, 1]).all()
     assert np.isfinite(got[reset + 1:]).all()
     assert rel_err(got[reset + 1:], ref[reset + 1:]) <= TOL["f32"] and rel_err(got[:, 2], ref[:, 2]) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("variant", ["mamba2", "gdn"])
+@pytest.mark.parametrize("dtype,d,rep", [("bf16", (128, 128), 1), ("bf16", (128, 64), 50), ("f32", (64, 64), 43), ("f32", (16, 16), 1)])
+def test_rows_that_begin_at_any_element(variant, dtype, d, rep):
+    """q, k and v one element past an aligned address: the same bits as from aligned ones."""
+    import torch
+    x = inputs(variant, dtype, d, 40)
+    a, b = (Decoder(variant, x, dtype, fenwick.num_levels(40), rep) for _ in range(2))
+    for n in ("q", "k", "v"):
+        z = b.a[n]
+        b.a[n] = torch.cat([z.new_zeros(1), z.flatten()])[1:].view(z.shape)
+        assert b.a[n].data_ptr() % 16 == z.element_size()
+    assert (a.feed(0, 40) == b.feed(0, 40)).all()
