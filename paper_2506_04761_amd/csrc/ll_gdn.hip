@@ -82,8 +82,12 @@ __device__ inline int kfrag_idx(int k, int n) {
 // round trip less for half the chunks (160 -> 137 us); the forward 513 -> 396 us.  Bound: bursts of memory
 // traffic at one workgroup per compute unit (stamps: of 51 thousand cycles per pair 13 to 20 thousand wait for
 // staging or behind stores; the fp32 output between kernels is the largest item, 64 KB per pair), then the
-// serial inversion.  A sequence of two chunks has half the workgroups: T = 128, 8 heads, d = 64 takes 15.6 us
-// where single chunks took 14.3; from 16 chunks on pairs win (T = 2048: 32.0 -> 31.3 us).
+// serial inversion.
+//
+// ONE (sequences of one or two chunks): no tree and no read-out follow, so P, H, Qc and chunk 1's W_1', U_1' are not
+// formed, the output leaves as bf16 rows at once, and where sequences have one chunk the halves take one each.
+// T = 64 / 128, d = 128: 12.5 / 14.3 us (8 heads), 14.4 / 32.2 us (512), with everything formed and read out 21.2 / 21.6 and
+// 47.8 / 57.2 us; one chunk per workgroup took 17.8 / 20.0 and 36.6 / 69.3.
 // ---------------------------------------------------------------------------------------------
 template <int DK, int DV>
 struct PairHalf {  // LDS of one half
@@ -115,13 +119,14 @@ __device__ inline bf16x8 pair_rows(bf16x4 x, bf16x4 y) {
 __device__ inline int blk_at(int r, int c) { return r * 16 + ((((c >> 2) ^ (r >> 1)) & 3) << 2) + (c & 3); }
 __device__ inline int blk(int i, int j) { return (i * (i + 1) / 2 + j) * 256; }
 
-template <int DK, int DV, bool HAS_LAMBDA>
+template <int DK, int DV, bool HAS_LAMBDA, bool ONE>
 __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, const bf* __restrict__ k,
                                                      const bf* __restrict__ v, const float* __restrict__ log_alpha,
                                                      const float* __restrict__ beta, const float* __restrict__ lam,
                                                      bf* __restrict__ qc_out, bf* __restrict__ pz_out,
                                                      bf* __restrict__ hz_out, float* __restrict__ oin_out,
-                                                     int64_t Tlen, int H, int L, int64_t npairs) {
+                                                     bf* __restrict__ o_out, int64_t Tlen, int H, int L,
+                                                     int64_t npairs, int64_t nseq) {
   using M = Mfma<bf>;
   typedef M::frag frag;
   constexpr int C = 64, KS = DK / 32, KT = DK / 16, VT = DV / 16, NL = 8;  // NL: levels inside a pair
@@ -156,6 +161,15 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
   auto where = [&](int64_t it) {
     Where x;
     const int64_t work = xcd_remap(it, npairs);
+    if (ONE && N == 1) {  // the halves take two sequences
+      const int64_t seq = 2 * work + hf;
+      x.valid = seq < nseq;
+      x.zp = 0;
+      x.bh = x.valid ? seq : nseq - 1;
+      x.h = (int)(x.bh % H);
+      x.tok0 = (x.bh / H) * Tlen;
+      return x;
+    }
     x.zp = work % N2;
     x.bh = work / N2;
     x.h = (int)(x.bh % H);
@@ -367,6 +381,8 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
       ureg[mt] = M::mma(frag_down_rows_swz<DV>(S.v, 32, 16 * mt, lane), zf[1], ureg[mt]);
     }
   }
+  // ONE: the output transposed, so that a lane holds four columns of its row
+  auto out_mma = [](frag a, frag b, f32x4 c) { return ONE ? M::mma(b, a, c) : M::mma(a, b, c); };
   // ---- A_c^T = T_G^T P_G^T, masked by the levels of the chunk; intra-chunk output rows t
   f32x4 oacc[VT];
   {
@@ -388,15 +404,15 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
     const frag a0 = join(a4[0], a4[1]), a1 = join(a4[2], a4[3]);
 #pragma unroll
     for (int vt = 0; vt < VT; ++vt) {
-      oacc[vt] = M::mma(a0, frag_down_rows_swz<DV>(S.v, 0, 16 * vt, lane), zero4());
-      oacc[vt] = M::mma(a1, frag_down_rows_swz<DV>(S.v, 32, 16 * vt, lane), oacc[vt]);
+      oacc[vt] = out_mma(a0, frag_down_rows_swz<DV>(S.v, 0, 16 * vt, lane), zero4());
+      oacc[vt] = out_mma(a1, frag_down_rows_swz<DV>(S.v, 32, 16 * vt, lane), oacc[vt]);
     }
   }
   __syncthreads();  // W of both chunks
 
   // ---- Qc^T = gamma Q^T - W^T P_G^T (columns t); U over the wave's own rows of Q
   f32x4 qc[KT];
-  {
+  if (!ONE || (hf == 1 && N > 1)) {
     const float gt = S.gm[t_own];
 #pragma unroll
     for (int mt = 0; mt < KT; ++mt) {
@@ -412,16 +428,26 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
   float* oin = oin_out + cidx * (C * DV) + w * (VT * 256) + 4 * lane;
   // U of chunk 1 in fp32, handed to the wave of chunk 0 that continues it, over V (no longer read)
   float* u1 = reinterpret_cast<float*>(w < 2 ? S1.v : S0.v) + (w & 1) * (VT * 256) + 4 * lane;
+  bf* o_row = o_out + ((cur.tok0 + t_own) * H + cur.h) * DV + 16 * (g & 1) + 8 * (g >> 1);
+  auto store_out = [&]() {  // rows of the output, as those of Qc
+#pragma unroll
+    for (int vt = 0; vt < VT; vt += 2)
+      *reinterpret_cast<bf16x8*>(o_row + 16 * vt) = pair_rows(pack(oacc[vt]), pack(oacc[vt + 1]));
+  };
   if (hf == 0) {
 #pragma unroll
     for (int mt = 0; mt < VT; ++mt)
       *reinterpret_cast<bf16x4*>(S.q + swz<DV>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1)) = pack(ureg[mt]);
+    if constexpr (ONE) {
+      if (valid) store_out();
+    } else {
 #pragma unroll
-    for (int mt = 0; mt < KT; mt += 2)
-      *reinterpret_cast<bf16x8*>(qc_row + 16 * mt) = pair_rows(pack(qc[mt]), pack(qc[mt + 1]));
+      for (int mt = 0; mt < KT; mt += 2)
+        *reinterpret_cast<bf16x8*>(qc_row + 16 * mt) = pair_rows(pack(qc[mt]), pack(qc[mt + 1]));
 #pragma unroll
-    for (int vt = 0; vt < VT; ++vt) *reinterpret_cast<f32x4*>(oin + 256 * vt) = oacc[vt];
-  } else {
+      for (int vt = 0; vt < VT; ++vt) *reinterpret_cast<f32x4*>(oin + 256 * vt) = oacc[vt];
+    }
+  } else if constexpr (!ONE) {
 #pragma unroll
     for (int mt = 0; mt < VT; ++mt) *reinterpret_cast<f32x4*>(u1 + 256 * mt) = ureg[mt];
   }
@@ -439,7 +465,7 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
       out[st] = acc * *reinterpret_cast<const f32x4*>(&S0.dc[16 * st + 4 * g]);
     }
   };
-  if (hf == 1) {
+  if (hf == 1 && (!ONE || N > 1)) {
     const float l7 = HAS_LAMBDA ? lam_h[t_own * NL + NL - 1] : 1.f;
     frag gq[2], gl[2];  // the second times lambda
     {
@@ -454,26 +480,28 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
         gl[ks] = join(pack(aq[2 * ks] * l7), pack(aq[2 * ks + 1] * l7));
       }
     }
+    if constexpr (!ONE) {
 #pragma unroll
-    for (int mt = 0; mt < KT; ++mt) {
-      f32x4 x = M::mma(frag_down_rows_swz<DK>(S0.w, 0, 16 * mt, lane), gq[0], zero4());
-      x = M::mma(frag_down_rows_swz<DK>(S0.w, 32, 16 * mt, lane), gq[1], x);
+      for (int mt = 0; mt < KT; ++mt) {
+        f32x4 x = M::mma(frag_down_rows_swz<DK>(S0.w, 0, 16 * mt, lane), gq[0], zero4());
+        x = M::mma(frag_down_rows_swz<DK>(S0.w, 32, 16 * mt, lane), gq[1], x);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) qc[mt][r] = g0 * qc[mt][r] - x[r];
+        for (int r = 0; r < 4; ++r) qc[mt][r] = g0 * qc[mt][r] - x[r];
+      }
     }
 #pragma unroll
     for (int vt = 0; vt < VT; ++vt) {
-      oacc[vt] = M::mma(gl[0], frag_down_rows_swz<DV>(S0.q, 0, 16 * vt, lane), oacc[vt]);
-      oacc[vt] = M::mma(gl[1], frag_down_rows_swz<DV>(S0.q, 32, 16 * vt, lane), oacc[vt]);
+      oacc[vt] = out_mma(gl[0], frag_down_rows_swz<DV>(S0.q, 0, 16 * vt, lane), oacc[vt]);
+      oacc[vt] = out_mma(gl[1], frag_down_rows_swz<DV>(S0.q, 32, 16 * vt, lane), oacc[vt]);
     }
-    if (valid) {
+    if (!ONE && valid) {
 #pragma unroll
       for (int mt = 0; mt < KT; mt += 2)
         *reinterpret_cast<bf16x8*>(qc_row + 16 * mt) = pair_rows(pack(qc[mt]), pack(qc[mt + 1]));
 #pragma unroll
       for (int vt = 0; vt < VT; ++vt) *reinterpret_cast<f32x4*>(oin + 256 * vt) = oacc[vt];
     }
-  } else {
+  } else if (!ONE) {
     auto w_at = [&](int mt) { return reinterpret_cast<bf16x4*>(S1.w + swz<DK>(t_own, 2 * mt + (g >> 1)) + 4 * (g & 1)); };
     frag wf[KS], gw[2];
     f32x4 aw[4];
@@ -498,13 +526,18 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
       *reinterpret_cast<bf16x4*>(S1.q + swz<DV>(t_own, 2 * vt + (g >> 1)) + 4 * (g & 1)) = pack(u - x);
     }
   }
-  __syncthreads();  // W_1', U_1'
+  if constexpr (ONE) {
+    if (hf == 1 && valid) store_out();
+  } else {
+    __syncthreads();  // W_1', U_1'
+  }
 
   // ---- P = gamma_0 gamma_1 I - K~^T W (half 0) and H = K~^T U (half 1) over the pair's 128 tokens: RT row
   //      tiles of d_k per wave, their K~ fragments scaled once, each operand of W or U read for all of them
   constexpr int RT = KT / 4;
   const float gt1 = S1.gm[C - 1], gp = g0 * gt1;
   frag ka[RT][4];
+  if constexpr (!ONE)
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const PairHalf<DK, DV>& X = half_s[ks >> 1];
@@ -568,6 +601,7 @@ __global__ __launch_bounds__(512, 2) void k_gdn_pair(const bf* __restrict__ q, c
       }
     }
   };
+  if constexpr (ONE) continue;
   bf* pz = pz_out + (bh * N2 + zp) * (DK * DK);
   bf* hz = hz_out + (bh * N2 + zp) * (DK * DV);
   if (hf == 1) products(std::false_type{}, std::false_type{}, hz);
@@ -895,7 +929,7 @@ hipError_t launch_gdn(const GdnArgs& a, hipStream_t st, hipEvent_t* ev) {
   const int J = N2 <= 1 ? 0 : 64 - __builtin_clzll(uint64_t(N2 - 1));
   const int64_t nchunks = a.B * a.H * N;
   // the pair kernel runs one persistent workgroup per compute unit
-  const int64_t npairs = a.B * a.H * N2;
+  const int64_t npairs = N == 1 ? (a.B * a.H + 1) / 2 : a.B * a.H * N2;
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
     ncu = 256;
@@ -905,12 +939,15 @@ hipError_t launch_gdn(const GdnArgs& a, hipStream_t st, hipEvent_t* ev) {
   const __bf16* v = static_cast<const __bf16*>(a.v);
   __bf16* o = static_cast<__bf16*>(a.o);
   if (ev) (void)hipEventRecord(ev[0], st);
-  if (a.lambda)
-    hipLaunchKernelGGL((gdn::k_gdn_pair<DK, DV, true>), g1, dim3(512), 0, st, q, k, v, a.log_alpha, a.beta, a.lambda, qc,
-                       pz, hz, oin, a.T, (int)a.H, a.L, npairs);
-  else
-    hipLaunchKernelGGL((gdn::k_gdn_pair<DK, DV, false>), g1, dim3(512), 0, st, q, k, v, a.log_alpha, a.beta, a.lambda,
-                       qc, pz, hz, oin, a.T, (int)a.H, a.L, npairs);
+  auto launch_pair = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, g1, dim3(512), 0, st, q, k, v, a.log_alpha, a.beta, a.lambda, qc, pz, hz, oin, o, a.T,
+                       (int)a.H, a.L, npairs, a.B * a.H);
+  };
+  const bool one = N2 == 1;  // no tree, nothing to read out
+  if (a.lambda && one) launch_pair(gdn::k_gdn_pair<DK, DV, true, true>);
+  else if (a.lambda) launch_pair(gdn::k_gdn_pair<DK, DV, true, false>);
+  else if (one) launch_pair(gdn::k_gdn_pair<DK, DV, false, true>);
+  else launch_pair(gdn::k_gdn_pair<DK, DV, false, false>);
   if (ev) (void)hipEventRecord(ev[1], st);
   // the block tree, one level per launch (level m from level m - 1; level 0 = P_z, H_z)
   __bf16* tree = reinterpret_cast<__bf16*>(base + w.tree);
@@ -924,13 +961,12 @@ hipError_t launch_gdn(const GdnArgs& a, hipStream_t st, hipEvent_t* ev) {
     hipLaunchKernelGGL((gdn::k_gdn_combine<DK, DV>), dim3((unsigned)((N2 >> m) * split), (unsigned)BH), dim3(256), 0, st,
                        tin, ain, ts, as, nin, tree + gdn::tree_level_offset(BH, N2, m, BS), N2 >> m);
   }
-  const dim3 g2((unsigned)nchunks);
-  if (a.lambda)
-    hipLaunchKernelGGL((gdn::k_gdn_read<C, DK, DV, true>), g2, dim3(256), 0, st, a.lambda, qc, pz, hz, tree, oin, o,
-                       a.T, (int)a.H, a.L, (int)BH);
-  else
-    hipLaunchKernelGGL((gdn::k_gdn_read<C, DK, DV, false>), g2, dim3(256), 0, st, a.lambda, qc, pz, hz, tree, oin, o,
-                       a.T, (int)a.H, a.L, (int)BH);
+  auto launch_read = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nchunks), dim3(256), 0, st, a.lambda, qc, pz, hz, tree, oin, o, a.T,
+                       (int)a.H, a.L, (int)BH);
+  };
+  if (!one && a.lambda) launch_read(gdn::k_gdn_read<C, DK, DV, true>);
+  else if (!one) launch_read(gdn::k_gdn_read<C, DK, DV, false>);
   if (ev) (void)hipEventRecord(ev[2], st);
   return hipGetLastError();
 }

@@ -1,7 +1,7 @@
 """Log-linear Gated DeltaNet by pairs of chunks (the unit of the WY kernel, the tree and the read-out) where
-pairs can go wrong: an odd chunk count leaves the last pair half full, and more pairs than compute units
-give the persistent workgroups a second turn for some of them.  Sampled heads against the float64
-quadratic form; bf16 inputs with fp32 accumulation, normalised max-abs error <= 2e-2 as for the forward."""
+pairs can go wrong: an odd chunk count leaves the last pair half full, sequences of one or two chunks have
+no tree and no read-out, and more pairs than compute units give the persistent workgroups a second turn for
+some of them.  Sampled heads against the float64 quadratic form; bf16 inputs with fp32 accumulation, normalised max-abs error <= 2e-2 as for the forward."""
 
 import numpy as np
 import pytest
@@ -15,7 +15,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,H,chunks", [
-    (1, 300, 1),  # half-full pairs only, 300 of them on 256 compute units
+    (1, 300, 1),  # one chunk each: a workgroup takes two sequences
+    (1, 515, 1),  # 258 of them on 256 compute units, the last with one sequence
+    (3, 1, 1),
+    (1, 300, 2),  # one full pair each, 300 on 256 compute units
     (2, 70, 3),   # 280 pairs: full and half-full ones in turn
     (3, 40, 5),   # 360 pairs, a tree of one level over an odd pair count
     (1, 90, 6),   # 270 full pairs
