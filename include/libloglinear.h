@@ -266,7 +266,10 @@ ll_status ll_mamba2_bwd_staged(const void* q, const void* k, const void* v, cons
  * [B, H, L] float32 (lambda == NULL: all level weights 1, i.e. Mamba-2 decoding).  Supported
  * (dtype, d_k, d_v): fp32 (16, 16), (64, 64); bf16 (64, 64), (128, 64), (128, 128).  Steps on one
  * state must be enqueued in token order on one stream (each step reads what the previous one
- * wrote); the state is read and written in place. */
+ * wrote); the state is read and written in place.  How much of it a step reads and writes varies:
+ * for all but small batches the last tokens (8 to 32) are kept as they came, and every 8th to 32nd
+ * step, which turns them into levels, takes longer than the others.  Steps of fp32 and of bf16 may
+ * follow each other on one state where both are supported. */
 
 /* Bytes of decode state for these sizes; 0 if an argument is < 1.  Pure host function. */
 size_t ll_decode_state_bytes(int64_t B, int64_t H, int64_t d_k, int64_t d_v, int32_t L);
@@ -286,8 +289,7 @@ ll_status ll_mamba2_decode_step(const void* q, const void* k, const void* v, con
 
 /* Log-linear Gated DeltaNet decoding with the same state buffer (ll_decode_state_bytes) and
  * conventions.  Token t applies the gated delta-rule transition alpha_t (I - beta_t k_t k_t^T) to
- * every carried and merged level (Sec. 3.2 merges; every nonempty level is rewritten each step),
- * then beta_t v_t k_t^T enters level 0; o_t = sum_l lambda_t^(l) S_t^(l) q_t.  beta [B, H] is
+ * every carried and merged level (Sec. 3.2 merges), then beta_t v_t k_t^T enters level 0; o_t = sum_l lambda_t^(l) S_t^(l) q_t.  beta [B, H] is
  * float32 and required; lambda == NULL gives Gated DeltaNet decoding.  Feeding tokens 0..T-1 gives
  * the rows of the log-linear Gated DeltaNet forward.  Same shapes, checks and statuses as the
  * Mamba-2 calls (a state is used by one variant between initialisations). */

@@ -364,10 +364,10 @@ __global__ __launch_bounds__(kDecodeThreads) void k_decode_step(
 // the transitions to every level at each token instead reads and writes all of them each step.  The
 // step that opens the next window (t % W == 0) applies the full window's W transitions to every level,
 // row by row in registers, adds the window's own tokens to the merged one and writes them all.
-// 1024 heads, d = 128, bf16, positions 3000 .. 3031: 208 -> 71 us a step on average, its merge about 290.
-// W = 16 against 32: 57.2 / 56.7 us (1024 heads, positions 1984 .. 2111), 20.8 / 23.5 (256 heads), 74.1 /
-// 70.5 (1024 heads, positions 3000 .. 3031).  Registers bound the waves in flight: the Gram rows in
-// registers instead of LDS, or spilling to 80 or 64 of them, cost 7 to 60 % of the step.
+// 1024 heads, d = 128, bf16, W = 32, positions 2976 .. 3039: 208 -> 72 us a step on average, the merges in it 193,
+// where the worst step that rewrites every level took 263 (decode_log_window: other batches).  Registers bound
+// the waves in flight: the Gram rows in registers instead of LDS, or spilling to 80 or 64 of them, cost 7 to
+// 60 % of the step.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int DK, int DV, int LOGW, int RB>
 __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kDecodeThreads) void k_gdn_decode_step(
 // its window.  The merged level p + 1 is the sum of levels LOGW + 1 .. p before them and of the window's
 // tokens, which enter in turn (x <- alpha_s (x - beta_s (x . k_s) k_s) + beta_s v_s[row] k_s).
 // 8 lanes per row: the 2 DK / 8 multiplications and additions of a transition outweigh the lanes' sum
-// (16 lanes: 414 us for 6 levels of 1024 heads, d = 128; 8: 290).
+// (16 lanes: 414 us for 6 levels of 1024 heads, d = 128, W = 32; 8: 290).
 constexpr int kMergeLanes = 8;
 
 template <typename T, int DK, int DV, int LOGW>
@@ -743,7 +743,7 @@ __global__ void k_zero_f32(float* __restrict__ p, int64_t n) {
 
 // Rows of d_v per workgroup, in 16s: 4 once that still gives every CU several workgroups (a window's
 // scores are formed once per workgroup), else 1, so that a small batch spreads over the chip.
-// d = 128, 16 against 64 rows: 53.7 / 50.0 us and 29.1 / 25.9 us (Mamba-2, 1024 and 512 heads), 80.3 / 61.6
+// d = 128, W = 32, 16 against 64 rows: 53.7 / 50.0 us and 29.1 / 25.9 us (Mamba-2, 1024 and 512 heads), 80.3 / 61.6
 // and 44.0 / 31.7 us (Gated DeltaNet); 256 heads or fewer keep 16.
 template <int DV>
 bool decode_wide(int64_t BH) {
@@ -837,8 +837,8 @@ hipError_t launch_gdn_decode(const void* q, const void* k, const void* v, const 
 
 hipError_t launch_decode_init(void* state, int64_t B, int64_t H, int64_t dk, int64_t dv, int L, hipStream_t st) {
   const DecodeLayout d = decode_layout(B, H, dk, dv, L);
-  // the scales and level-0 factors of both parities; the level data is read only where a
-  // scale is nonzero, so it needs no clearing
+  // the scales and level-0 factors of both parities.  The rest needs no clearing: a step reads the levels that
+  // hold tokens by the bits of t (of Mamba-2 those whose scale is nonzero), and rows that earlier steps wrote
   float* p = reinterpret_cast<float*>(static_cast<char*>(state) + d.scale);
   const int64_t n = (d.total - d.scale) / 4;
   hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);

@@ -74,7 +74,8 @@ __device__ inline int kfrag_idx(int k, int n) {
 //
 // Registers carry what one wave both makes and uses: a product formed transposed (rows 4g + r, columns
 // lane % 16) is, packed to bf16, an operand of the next one, its k slots in the order of
-// frag_down_rows.  LDS per half: K, Q, V (row-major, swizzled; direct loads), T_G, and the fp32 blocks of
+// frag_down_rows.  LDS per half: K, Q, V (row-major, swizzled; loaded into registers while the previous
+// pair's last products run, and stored from there), T_G, and the fp32 blocks of
 // L and of the inverse, whose room W takes after the inversion; U takes Q's.
 //
 // B = 2, H = 16, T = 8192, d = 128: this kernel 184-190 us where the kernel working on single chunks took
