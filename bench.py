@@ -766,7 +766,7 @@ def main_decode(args, w, torch, ll):
     BH = w.B * w.H
     SZ4 = w.dk * w.dv * 4
     token_bytes = BH * ((2 * w.dk + 2 * w.dv) * 2 + 4 + 4 * L + (w.dv + w.dk) * 2 + (4 if gdn else 0))
-    window = 8 if w.dk == 16 else 32  # as the kernels keep it
+    window = 8 if w.dk == 16 else 32  # as the kernels keep it for the workloads' 1024 heads
     rw = np.array(decode_level_traffic(w.T, window, gdn)[w.T - M:], dtype=np.float64).mean(axis=0)
     per_step = BH * ((rw[0] + rw[1]) * SZ4 + rw[2] * (w.dk + w.dv) * (2 if w.dtype == "bf16" else 4)) + token_bytes
     note = ("per head: the nonempty level states read and those written when a window of tokens is merged, fp32, and "
